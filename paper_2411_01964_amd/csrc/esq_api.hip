@@ -66,9 +66,10 @@ struct Params {
 };
 
 struct MedTable {
-    uint2* tasks = nullptr;
+    uint2* tasks = nullptr;         // n_tasks, then in the column layout one uint32 per 64 of them
     uint2* medq = nullptr;
     uint32_t n_tasks = 0;
+    uint32_t n_multi = 0;           // column layout: primes that have tasks
 };
 
 // A device block of per-call scratch kept by the library.  A call takes the
@@ -104,12 +105,13 @@ struct Ctx {
     uint64_t* d_wheel2 = nullptr;
     uint64_t* d_wheel_s = nullptr;  // the two tables one position lower (search regions)
     uint64_t* d_wheel2_s = nullptr;
+    uint32_t* d_col = nullptr;      // column layout: its two tables
     hipMemPool_t pool = nullptr;    // per-call scratch when no cached block serves (stream-ordered)
     std::vector<ScratchBlock> scratch;  // per-call scratch blocks kept for reuse (under scr_mu)
     size_t scratch_bytes = 0;
     std::mutex scr_mu;
-    std::map<std::tuple<uint32_t, uint32_t, uint32_t, uint32_t, uint32_t>, MedTable> med;
-    std::map<std::tuple<int, uint32_t, size_t>, int> occupancy;  // (mode, block, LDS bytes) -> workgroups per CU
+    std::map<std::tuple<uint32_t, uint32_t, bool, uint32_t, uint32_t, uint32_t>, MedTable> med;
+    std::map<std::tuple<int, uint32_t, size_t>, int> occupancy;  // (kernel, block, LDS bytes) -> workgroups per CU
     uint64_t generation = 0;        // changes whenever a device table that a prepared batch holds is replaced
 };
 
@@ -266,6 +268,8 @@ void free_ctx(Ctx* c)
         (void)hipFree(c->d_primes);
     if (c->d_wheel)
         (void)hipFree(c->d_wheel);  // d_wheel2 lives in the same allocation
+    if (c->d_col)
+        (void)hipFree(c->d_col);
     if (c->pool || !c->scratch.empty())
         (void)hipDeviceSynchronize();  // no call may still hold scratch
     for (ScratchBlock& b : c->scratch) {
@@ -286,42 +290,70 @@ uint32_t prime_upper(const Ctx* c, uint64_t x)
                       c->primes.begin());
 }
 
-// Medium primes primes[kFirstMedium .. med_end) for a region of rw words and segment
+// Medium primes, up to primes[med_end - 1], for a region of rw words and segment
 // length S: per prime (q, S mod q), and lane-tasks -- prime i with up to
 // h = ceil(R / q) marks per region is split into c = ceil(h / entry_hits)
 // tasks; task v marks f + v q + t c q, t >= 0.  A task is packed as
-// x = v q | i << 21 (v q < R < 2^21; i < 2^11) and y = c q.
+// x = v q | i << 21 (v q < R < 2^21; i < 2^11) and y = c q, in the column
+// layout scaled as its marks step.
 //
 // Task e of the table is taken by thread e mod block.
-int get_med_table_locked(Ctx* c, uint32_t rw, uint32_t log2S, uint32_t med_end, uint32_t entry_hits,
+int get_med_table_locked(Ctx* c, uint32_t rw, uint32_t S, bool col, uint32_t med_end, uint32_t entry_hits,
                          uint32_t block, MedTable** out)
 {
-    const auto key = std::make_tuple(rw, log2S, med_end, entry_hits, block);
+    const auto key = std::make_tuple(rw, S, col, med_end, entry_hits, block);
     auto it = c->med.find(key);
     if (it != c->med.end()) {
         *out = &it->second;
         return ESQ_OK;
     }
     const uint64_t R = (uint64_t)rw * 64;
-    const uint64_t S = 1ull << log2S;
     const uint32_t nmed = med_end - kFirstMedium;
     if (R >= (1u << 21) || nmed > (1u << 11))
         return fail(ESQ_EINVAL, "medium-prime task packing: region or prime count too large");
-    std::vector<std::pair<uint64_t, uint2>> tasks;
     std::vector<uint2> medq(std::max<uint32_t>(nmed, 1));
+    auto hits = [&](uint32_t i) { return (R + medq[i].x - 1) / medq[i].x; };
     for (uint32_t i = 0; i < nmed; i++) {
         const uint64_t p = c->primes[kFirstMedium + i];
-        const uint64_t q = p * p;
-        medq[i].x = (uint32_t)q;
-        medq[i].y = (uint32_t)(S % q);
-        const uint64_t h = (R + q - 1) / q;
-        const uint64_t parts = std::max<uint64_t>(1, (h + entry_hits - 1) / entry_hits);
+        medq[i].x = (uint32_t)(p * p);
+        medq[i].y = (uint32_t)(S % (p * p));
+    }
+    // Column layout: only the primes with more than kColSingle marks have
+    // tasks, and these as few marks as one task per lane allows (a lane keeps
+    // its task in registers; a second round of tasks costs more than the
+    // marks that it takes from the first).
+    uint32_t n_multi = nmed, target = entry_hits;
+    if (col) {
+        for (n_multi = 0; n_multi < nmed && hits(n_multi) > kColSingle;)
+            n_multi++;
+        auto count = [&](uint32_t t) {
+            uint64_t n = 0;
+            for (uint32_t i = 0; i < n_multi; i++)
+                n += (hits(i) + t - 1) / t;
+            return n;
+        };
+        while (target > 1 && count(target - 1) <= block)
+            target--;
+    }
+    struct Task {
+        uint64_t most, least;  // marks in a region
+        uint2 t;
+    };
+    std::vector<Task> tasks;
+    for (uint32_t i = 0; i < n_multi; i++) {
+        const uint64_t q = medq[i].x, h = hits(i);
+        const uint64_t parts = std::max<uint64_t>(1, (h + target - 1) / target);
         for (uint64_t v = 0; v < parts; v++) {
             // v q <= (h - 1) q < R; c q <= R + q when c > 1, else q
-            uint2 t;
-            t.x = (uint32_t)(v * q) | (i << 21);
-            t.y = (uint32_t)(parts * q);
-            tasks.push_back({(h + parts - 1) / parts, t});
+            Task k;
+            k.t.x = (uint32_t)(v * q) | (i << 21);
+            k.t.y = (uint32_t)(parts * q);
+            if (col)
+                k.t.y = parts * q >= R ? ~0u : k.t.y << (32 - kColLog2);
+            k.most = (h + parts - 1) / parts;
+            // its first mark lies below c q, so floor(R / (c q)) of them fit
+            k.least = R / (parts * q);
+            tasks.push_back(k);
         }
     }
     // lanes of one wave get tasks of similar length (dealing groups of 64 to
@@ -329,12 +361,20 @@ int get_med_table_locked(Ctx* c, uint32_t rw, uint32_t log2S, uint32_t med_end, 
     // slower: the waves that finish early hand their SIMD to other
     // workgroups' search)
     std::stable_sort(tasks.begin(), tasks.end(),
-                     [](const auto& a, const auto& b) { return a.first > b.first; });
+                     [](const Task& a, const Task& b) { return a.most > b.most; });
     std::vector<uint2> host(tasks.size());
     for (size_t i = 0; i < tasks.size(); i++)
-        host[i] = tasks[i].second;
+        host[i] = tasks[i].t;
+    if (col) {
+        std::vector<uint32_t> least((tasks.size() + 127) / 128 * 2, ~0u);
+        for (size_t i = 0; i < tasks.size(); i++)
+            least[i / 64] = std::min(least[i / 64], (uint32_t)tasks[i].least);
+        for (size_t i = 0; i < least.size(); i += 2)
+            host.push_back(uint2{least[i], least[i + 1]});
+    }
     MedTable t;
-    t.n_tasks = (uint32_t)host.size();
+    t.n_tasks = (uint32_t)tasks.size();
+    t.n_multi = n_multi;
     hipError_t e = hipMalloc(&t.medq, medq.size() * sizeof(uint2));
     if (e != hipSuccess)
         return hip_fail(e, "hipMalloc(medium primes)");
@@ -360,20 +400,22 @@ int get_med_table_locked(Ctx* c, uint32_t rw, uint32_t log2S, uint32_t med_end, 
     return ESQ_OK;
 }
 
-int get_med_table(Ctx* c, uint32_t rw, uint32_t log2S, uint32_t med_end, uint32_t entry_hits,
+int get_med_table(Ctx* c, uint32_t rw, uint32_t S, bool col, uint32_t med_end, uint32_t entry_hits,
                   uint32_t block, MedTable** out)
 {
     std::lock_guard<std::mutex> lk(g_mu);
-    return get_med_table_locked(c, rw, log2S, med_end, entry_hits, block, out);
+    return get_med_table_locked(c, rw, S, col, med_end, entry_hits, block, out);
+}
+
+uint32_t floor_mod(int64_t x, uint32_t m)
+{
+    const int64_t r = x % (int64_t)m;
+    return (uint32_t)(r < 0 ? r + (int64_t)m : r);
 }
 
 uint32_t wheel_base(int64_t region_start)
 {
-    const int64_t g = region_start / 64;  // exact, region_start is a multiple of 64
-    int64_t r = g % (int64_t)kWheelPeriod;
-    if (r < 0)
-        r += kWheelPeriod;
-    return (uint32_t)r;
+    return floor_mod(region_start / 64, kWheelPeriod);  // exact, region_start is a multiple of 64
 }
 
 size_t align_up(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -407,19 +449,57 @@ uint32_t block_for(const Params& par, int mode, uint32_t n_iv)
     return (uint32_t)(mode == 2 ? par.sieve_block : mode == 1 && n_iv == 1 ? par.per_n_block : par.block);
 }
 
-// The medium-prime tables of the verify geometry for the current knobs (at
-// the summary and the per-n block size), made at set-up (esq_init,
-// esq_set_param; g_mu held) so that calls find them resident.
+// Segment geometry of a launch: S odd numbers per segment, the region's words
+// around them, and the segment kernel's mode.
+struct Geometry {
+    uint32_t S, hlo, hup, rw, kmode;
+    bool col;
+};
+
+// mode 0 verify, 1 per-n, 2 sieve alone; klds the deepest step searched in LDS.
+// The halo below a segment holds the candidates of depth up to kh, also when
+// kmax is smaller (a larger halo is harmless): the geometry, and with it the
+// medium-prime tables, depends on the knobs only.
+// Summary mode takes the column layout (k_column) at the segment length, halo
+// (kh = 13) and block size that its one instance is compiled for, where the
+// search goes past the four steps that it runs without a level bound.
+Geometry geometry(const Params& par, int mode, uint32_t klds)
+{
+    Geometry g;
+    std::memset(&g, 0, sizeof(g));
+    g.kmode = (uint32_t)mode;
+    if (mode == 2) {
+        g.hup = 1;
+        g.S = 1u << par.sieve_seg_log2;
+    } else {
+        g.hlo = (par.kh >= 7 ? (1u << (par.kh - 1)) : 64u) / 64;
+        g.S = 1u << par.seg_log2;
+        g.col = mode == 0 && klds >= 5 && g.hlo * 64 == kColHalo && par.seg_log2 == kColLog2 &&
+                par.block == (int)kColBlock;
+        if (g.col) {
+            g.kmode = 3;
+            g.S = (1u << kColLog2) - kColHalo;
+            g.rw = (1u << kColLog2) / 64;
+            return g;
+        }
+    }
+    g.rw = g.hlo + g.S / 64 + g.hup;
+    return g;
+}
+
+// The medium-prime tables of the verify geometries for the current knobs
+// (summary, per-n, and summary with a bounded search), made at set-up
+// (esq_init, esq_set_param; g_mu held) so that calls find them resident.
 int prebuild_med_table(Ctx* c, const Params& par)
 {
-    const uint32_t med_end = medium_end(c, par);
-    if (med_end <= kFirstMedium)
-        return ESQ_OK;
-    const uint32_t hlo = (par.kh >= 7 ? (1u << (par.kh - 1)) : 64u) / 64;
-    const uint32_t rw = hlo + (uint32_t)((1ull << par.seg_log2) / 64);
     MedTable* mt = nullptr;
-    for (int mode = 0; mode < 2; mode++) {
-        const int rc = get_med_table_locked(c, rw, (uint32_t)par.seg_log2, med_end, (uint32_t)par.entry_hits,
+    for (int v = 0; v < 3; v++) {
+        const int mode = v == 1 ? 1 : 0;
+        const Geometry g = geometry(par, mode, v == 2 ? 1u : (uint32_t)par.kh);
+        const uint32_t med_end = medium_end(c, par);
+        if (med_end <= kFirstMedium)
+            continue;
+        const int rc = get_med_table_locked(c, g.rw, g.S, g.col, med_end, (uint32_t)par.entry_hits,
                                             block_for(par, mode, 1), &mt);
         if (rc)
             return rc;
@@ -453,22 +533,14 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
          bool exc_list, Planned* P, bool no_alloc = false)
 {
     const uint32_t n_iv = (uint32_t)reqs.size();
-    const uint32_t log2S = (uint32_t)(mode == 2 ? par.sieve_seg_log2 : par.seg_log2);
     const uint32_t blk = block_for(par, mode, n_iv);
-    const uint64_t S = 1ull << log2S;
-    const uint32_t SW = (uint32_t)(S / 64);
     const uint32_t kmax_eff = kmax ? kmax : 63;
     const uint32_t klds = std::min<uint32_t>(kmax_eff, (uint32_t)par.kh);
-    // The halo below a segment holds the candidates of depth up to kh, also
-    // when kmax is smaller (a larger halo is harmless): the geometry, and with
-    // it the medium-prime tables, depends on the knobs only.
-    uint32_t hlo = 0, hup = 0;
-    if (mode == 2) {
-        hup = 1;
-    } else {
-        hlo = (par.kh >= 7 ? (1u << (par.kh - 1)) : 64u) / 64;
-    }
-    const uint32_t rw = hlo + SW + hup;
+    const Geometry geo = geometry(par, mode, klds);
+    const uint64_t S = geo.S;
+    const uint32_t SW = (uint32_t)(S / 64);
+    const uint32_t hlo = geo.hlo, hup = geo.hup, rw = geo.rw;
+    const bool col = geo.col;
     const uint64_t R = (uint64_t)rw * 64;
 
     // per-interval geometry
@@ -482,7 +554,7 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
         std::memset(&v, 0, sizeof(v));
         v.I0 = r.I0;
         v.I1 = r.I1;
-        v.A0 = (int64_t)(r.I0 & ~63ull);
+        v.A0 = (int64_t)(col ? r.I0 : r.I0 & ~63ull);
         v.out_mink = r.out_mink;
         v.out_bits = r.out_bits;
         v.out_shift = (uint32_t)(r.I0 - (uint64_t)v.A0);
@@ -505,7 +577,8 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
         nseg_total += nseg;
         if (nseg_total > 0x7fffffffull)
             return fail(ESQ_ERANGE, "too many segments in one call");
-        v.wheel_base0 = wheel_base(v.A0 - (int64_t)hlo * 64);
+        v.wheel_base0 = col ? floor_mod(v.A0 - (int64_t)hlo * 64 - 1, kWheelPeriod)
+                            : wheel_base(v.A0 - (int64_t)hlo * 64);
         pmax_all = std::max(pmax_all, pmax[i]);
     }
 
@@ -596,12 +669,12 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
         if (no_alloc) {
             // only a table made at set-up: making one here would allocate
             std::lock_guard<std::mutex> lk(g_mu);
-            auto it = c->med.find(std::make_tuple(rw, log2S, med_end, (uint32_t)par.entry_hits,
+            auto it = c->med.find(std::make_tuple(rw, geo.S, geo.col, med_end, (uint32_t)par.entry_hits,
                                                   blk));
             if (it == c->med.end())
                 return fail(ESQ_ENOMEM, "medium-prime tables for these knobs are not resident");
             mt = &it->second;
-        } else if ((rc = get_med_table(c, rw, log2S, med_end, (uint32_t)par.entry_hits,
+        } else if ((rc = get_med_table(c, rw, geo.S, geo.col, med_end, (uint32_t)par.entry_hits,
                                        blk, &mt))) {
             return rc;
         }
@@ -621,24 +694,25 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     // LDS of the segment kernel: bitmap + medium-prime tables (+ tasks if they fit)
     const uint32_t nmed = med_end - kFirstMedium;
     const uint32_t n_tasks = mt ? mt->n_tasks : 0;
-    if (verify_lds_size(rw, nmed, 0, false, blk) > kVerifyLdsMax)
+    const uint32_t lds_rw = rw + (col ? kColGuard / 2 : 0u);
+    if (verify_lds_size(lds_rw, nmed, 0, false, blk) > kVerifyLdsMax)
         return fail(ESQ_EINVAL, "segment too large for LDS with these medium primes");
     // per-n output is staged through LDS (1 KB contiguous per store) when the
     // staging area fits beside the bitmap
-    const bool stage = mode == 1 && verify_lds_size(rw, nmed, 0, true, blk) <= kVerifyLdsMax;
-    const size_t lds_base = verify_lds_size(rw, nmed, 0, stage, blk);
+    const bool stage = mode == 1 && verify_lds_size(lds_rw, nmed, 0, true, blk) <= kVerifyLdsMax;
+    const size_t lds_base = verify_lds_size(lds_rw, nmed, 0, stage, blk);
     auto occupancy = [&](size_t bytes) {
         std::lock_guard<std::mutex> lk(g_mu);
-        const auto key = std::make_tuple(mode, blk, bytes);
+        const auto key = std::make_tuple((int)geo.kmode, blk, bytes);
         auto it = c->occupancy.find(key);
         if (it == c->occupancy.end())
-            it = c->occupancy.emplace(key, verify_occupancy(mode, blk, bytes)).first;
+            it = c->occupancy.emplace(key, verify_occupancy((int)geo.kmode, blk, bytes)).first;
         return it->second;
     };
     // the task table goes into LDS when it fits and costs no resident workgroup
-    const size_t lds_with = verify_lds_size(rw, nmed, n_tasks, stage, blk);
-    const bool tasks_in_lds = n_tasks == 0 || (lds_with <= kVerifyLdsMax &&
-                                               occupancy(lds_with) >= occupancy(lds_base));
+    const size_t lds_with = verify_lds_size(lds_rw, nmed, n_tasks, stage, blk);
+    const bool tasks_in_lds = !col && (n_tasks == 0 || (lds_with <= kVerifyLdsMax &&
+                                               occupancy(lds_with) >= occupancy(lds_base)));
     const size_t lds_bytes = tasks_in_lds ? lds_with : lds_base;
 
     // work items: runs of consecutive segments
@@ -646,8 +720,20 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     const uint64_t resident = (uint64_t)c->n_cu * (uint64_t)occ;
     std::vector<uint4>& items = P->items;
     items.clear();
-    uint32_t n_items = 0;
-    if (n_iv == 1) {
+    uint32_t n_items = 0, run_long = 0, run_short = 0;
+    const uint64_t per_wg = nseg_total / resident;
+    if (n_iv == 1 && col && par.runs_per_wg == 1 && per_wg >= 24) {
+        // One long run per resident workgroup, then the last quarter in short
+        // runs from the queue: workgroups that share a CU drift apart by a
+        // tenth of the kernel's time, and equal runs leave the CUs part empty
+        // at the end.  Below 24 segments a workgroup a run's own start (first
+        // hits, queue: about one segment's time) costs what the balance gives
+        // (2^32 odd n: 105 us equal, 115 us cut; 2^33: 181 us equal, 174 us cut).
+        run_long = (uint32_t)std::min<uint64_t>(kFlushSegs, per_wg * 3 / 4);
+        run_short = (uint32_t)std::min<uint64_t>(kFlushSegs, per_wg / 12);
+        const uint64_t rest = nseg_total - resident * run_long;
+        n_items = (uint32_t)(resident + (rest + run_short - 1) / run_short);
+    } else if (n_iv == 1) {
         // runs_per_wg runs per resident workgroup (a device-scope queue
         // operation costs microseconds, so runs stay few), each at most
         // kFlushSegs segments
@@ -699,13 +785,16 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
 
     Launch& L = P->L;
     std::memset(&L, 0, sizeof(L));
-    L.log2S = log2S;
+    L.S = (uint32_t)S;
+    L.s_inv = ~0ull / S;
     L.hlo_words = hlo;
     L.hup_words = hup;
     L.rw = rw;
     L.n_iv = n_iv;
     L.n_items = n_items;
-    L.mode = (uint32_t)mode;
+    L.run_long = run_long;
+    L.run_short = run_short;
+    L.mode = geo.kmode;
     L.med_end = med_end;
     L.n_tasks = n_tasks;
     L.tasks_in_lds = tasks_in_lds ? 1u : 0u;
@@ -733,6 +822,11 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     L.origin = mode == 2 ? 0u : 1u;
     L.wheel = mode == 2 ? c->d_wheel : c->d_wheel_s;
     L.wheel2 = mode == 2 ? c->d_wheel2 : c->d_wheel2_s;
+    if (col) {
+        L.col = c->d_col;
+        L.n_multi = mt ? mt->n_multi : 0;
+        L.task_min = mt ? reinterpret_cast<const uint32_t*>(mt->tasks + n_tasks) : nullptr;
+    }
     L.tail_cap = tail_cap;
     P->mode = mode;
     P->n_heavy = n_heavy;
@@ -1055,6 +1149,17 @@ int esq_init(int device, uint64_t max_hi)
             free_ctx(g_ctx);
             g_ctx = nullptr;
             return hip_fail(e, "k_wheel_build");
+        }
+        // the column layout's tables
+        if ((e = hipMalloc((void**)&g_ctx->d_col, kColTableWords * 4)) != hipSuccess) {
+            free_ctx(g_ctx);
+            g_ctx = nullptr;
+            return fail(ESQ_ENOMEM, "hipMalloc(column tables)");
+        }
+        if ((e = launch_col_build(g_ctx->d_col, nullptr)) != hipSuccess) {
+            free_ctx(g_ctx);
+            g_ctx = nullptr;
+            return hip_fail(e, "k_col_build");
         }
     }
     Ctx* c = g_ctx;

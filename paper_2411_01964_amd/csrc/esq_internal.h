@@ -13,6 +13,15 @@
 // segment's n up to depth kh fall inside LDS) and hup_words * 64 above it.
 // Bitmap bits are 1 for "not squarefree or not a positive odd number".
 //
+// Column layout (k_column).  A region is R = 32 W bits in W 32-bit words:
+// bit j of word i is odd index B1 + j W + i, so n - 2^k sits at the same bit
+// 2^(k-1) - 1 words lower (B1 is one odd index below the first n's halo): the
+// search's windows are plain reads of other words, where the row layout needs
+// two funnel shifts per step and word.  Word i - t < 0 is word W + i - t one
+// bit up; the bit that comes in is below the region, and only the halo's own
+// slots -- the first kColHalo positions, which are no n of the segment -- look
+// there.
+//
 // Work is a list of intervals; each interval is cut into segments, and runs
 // of consecutive segments ("items") are pulled by persistent workgroups from
 // a device queue.
@@ -26,6 +35,16 @@ constexpr uint32_t kWheelPeriod = 9u * 25u * 49u;  // 11025 words: the table sta
 constexpr uint32_t kWheelExtra = 16640;   // >= largest region in 64-bit words
 constexpr uint32_t kWheel2Period = 121u * 169u;  // 20449 words: second table (11^2, 13^2)
 constexpr size_t kWheelAlloc = 2u << 20;  // bytes holding both tables, at both origins
+// Column layout (k_column): summary mode at the default depth, segment length
+// and block size.
+constexpr int kColLog2 = 18;              // log2 of the region's bits
+constexpr uint32_t kColBlock = 512;       // threads per workgroup
+constexpr uint32_t kColHalo = 4096;       // region bits below the segment's first n
+constexpr uint32_t kColGuard = 32;        // 32-bit words below the region's word 0 in LDS
+constexpr uint32_t kColSingle = 3;        // primes with at most so many marks per region go without tasks
+// its two tables, in 32-bit words: one period and a region's words more each
+constexpr size_t kColTableWords = (size_t)kWheelPeriod + kWheel2Period + 2 * ((1u << kColLog2) / 32);
+
 constexpr uint32_t kFirstMedium = 5;      // primes[0 .. 5) = 3, 5, 7, 11, 13: the two tables
 constexpr int kMaxKh = 13;                // deepest in-LDS level supported
 constexpr int kMaxMedium = 1536;          // medium primes per launch (LDS offsets)
@@ -66,16 +85,20 @@ struct Interval {
 
 // Medium-prime lane-task, packed in a uint2: x = v q | (idx << 21), y = c q;
 // it marks f + v q + t c q, t >= 0, of medium prime idx (0 = the prime 17),
-// f its first hit in the region.
+// f its first hit in the region.  In the column layout y is the step scaled
+// by 2^(32 - kColLog2), or 2^32 - 1 where the step is no shorter than the region,
+// and only primes with more than one task have any.
 
 // Geometry and resources shared by every interval of a launch.
 struct Launch {
-    uint32_t log2S;
-    uint32_t hlo_words, hup_words, rw;  // rw = hlo_words + S/64 + hup_words
+    uint32_t S;                   // odd numbers per segment
+    uint64_t s_inv;               // floor((2^64 - 1) / S)
+    uint32_t hlo_words, hup_words, rw;  // rw = hlo_words + S/64 + hup_words (column layout: R/64)
     uint32_t n_iv;                // intervals
     uint32_t n_items;             // work items in the queue
+    uint32_t run_long, run_short; // one interval: see run_of
     uint32_t stage;               // per-n mode: depth bytes staged through LDS per wave
-    uint32_t mode;                // 0 verify, 1 verify + per-n, 2 sieve
+    uint32_t mode;                // 0 verify, 1 verify + per-n, 2 sieve, 3 verify in the column layout (k_column)
     uint32_t med_end;             // medium primes primes[kFirstMedium .. med_end)
     uint32_t n_tasks;
     uint32_t k_lds, kmax_eff;     // k_lds >= kmax_eff: every n unresolved in LDS is an exception
@@ -97,6 +120,9 @@ struct Launch {
     unsigned long long* phase;    // non-null: per-phase clock ticks of the segment loop (init, marking, search or store, segments)
     const uint64_t* wheel;        // kWheelPeriod + kWheelExtra words (9, 25, 49)
     const uint64_t* wheel2;       // kWheel2Period + kWheelExtra words (121, 169)
+    const uint32_t* col;          // column layout: its tables (9, 25, 49) and (121, 169)
+    uint32_t n_multi;             // column layout: the first n_multi of them go by lane-tasks
+    const uint32_t* task_min;     // column layout: marks that every task of a wave's 64 makes
     uint32_t origin;              // 1: a region's bit 0 is the odd index one below its word
                                   // boundary (search modes; wheel tables shifted to match)
     uint32_t* bucket_cnt;         // per global segment
@@ -111,6 +137,7 @@ struct Launch {
 
 // launchers (esq_kernels.hip); all return hipError_t of the launch
 hipError_t launch_wheel_build(uint64_t* wheel, uint64_t* wheel2, uint32_t shift, hipStream_t s);
+hipError_t launch_col_build(uint32_t* tab, hipStream_t s);
 hipError_t launch_prepare(const Launch& L, Acc* accs, const Interval* iv_single,
                           uint32_t nseg_total, hipStream_t s);
 hipError_t launch_bucket(const Launch& L, uint32_t n_heavy, uint32_t max_direct, uint32_t max_cof,
@@ -123,7 +150,7 @@ hipError_t configure_kernels();
 int verify_occupancy(int mode, uint32_t block, size_t lds_bytes);
 size_t verify_lds_bytes(const Launch& L, uint32_t block);
 constexpr size_t kVerifyLdsMax = 159 * 1024;  // dynamic LDS per workgroup
-constexpr uint32_t kVerifyCtrlWords = 28;       // k_verify's LDS control block, in 8-byte words
+constexpr uint32_t kVerifyCtrlWords = 28;       // the segment kernels' LDS control block, in 8-byte words
 constexpr uint32_t kPhaseSlots = 8;             // phase-clock counters (3 used)
 constexpr uint32_t kStageWordsPerWave = 528;    // per-n mode: one wave's 4096 depth bytes + 2 x 64 B guard
 

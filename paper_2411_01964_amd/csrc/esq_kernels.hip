@@ -8,6 +8,8 @@
 //                  that falls in a segment region goes to that segment's hit
 //                  slots (by first hit up to a cut-over chosen per launch, at
 //                  most 2^20; by cofactor enumeration above it)
+//   k_column       k_verify's summary form in the column layout: the default
+//                  for aggregates-only calls
 //   k_verify       persistent workgroups pull runs of consecutive segments;
 //                  per segment: Algorithm 1 in LDS, then Algorithm 2 as a
 //                  bit-sliced scan of the LDS bitmap (in per-n mode also one
@@ -62,8 +64,34 @@ hipError_t launch_wheel_build(uint64_t* wheel, uint64_t* wheel2, uint32_t shift,
     return hipGetLastError();
 }
 
+// Column layout: word x of a table marks, in bit j, odd index x + j W (W =
+// 2^kColLog2 / 32) modulo the table's period; W more words follow one period so
+// that a region's words are consecutive.  The tables lie one after the other.
+__global__ void k_col_build(uint32_t* tab)
+{
+    constexpr uint32_t W = (1u << kColLog2) / 32, n1 = kWheelPeriod + W, n2 = n1 + kWheel2Period + W;
+    for (uint32_t t = blockIdx.x * blockDim.x + threadIdx.x; t < n2; t += gridDim.x * blockDim.x) {
+        uint32_t word = 0;
+        for (uint32_t j = 0; j < 32; j++) {
+            const uint32_t x = (t < n1 ? t : t - n1) + j * W;
+            const bool hit = t < n1 ? (x % 9u == 4u || x % 25u == 12u || x % 49u == 24u)
+                                    : (x % 121u == 60u || x % 169u == 84u);
+            if (hit)
+                word |= 1u << j;
+        }
+        tab[t] = word;
+    }
+}
+
+hipError_t launch_col_build(uint32_t* tab, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_col_build, dim3(512), dim3(256), 0, s, tab);
+    return hipGetLastError();
+}
+
 typedef uint64_t u64x2 __attribute__((ext_vector_type(2), aligned(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
 
 // Output pointers read from an Interval in memory are generic: stores through
 // them become flat stores, which also count on the LDS wait counter, so every
@@ -184,10 +212,15 @@ __device__ __forceinline__ uint64_t isqrt_floor(uint64_t x)
 // belongs to segment floor(y / S) and to each earlier segment still reaching it.
 __device__ __forceinline__ void bucket_emit(const Launch& L, const Interval& iv, uint64_t y)
 {
-    const uint64_t S = 1ull << L.log2S;
+    const uint64_t S = L.S;
     const uint64_t R = (uint64_t)L.rw * 64;
-    uint64_t seg = y >> L.log2S;
-    uint64_t off = y & (S - 1);
+    // y div S through the reciprocal: at most one too small (y < 2^56)
+    uint64_t seg = __umul64hi(y, L.s_inv);
+    uint64_t off = y - seg * S;
+    if (off >= S) {
+        seg++;
+        off -= S;
+    }
     while (off < R) {
         if (seg < iv.nseg) {
             const uint32_t gs = iv.seg_base + (uint32_t)seg;
@@ -216,7 +249,7 @@ __global__ __launch_bounds__(256) void k_bucket(Launch L, uint32_t n_heavy, uint
     const Interval iv = L.iv[blockIdx.y];
     const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int64_t B0 = iv.A0 - (int64_t)L.hlo_words * 64 - (int64_t)L.origin;  // region bit 0
-    const uint64_t S = 1ull << L.log2S;
+    const uint64_t S = L.S;
     const uint64_t E = (uint64_t)(iv.nseg ? iv.nseg - 1 : 0) * S + (uint64_t)L.rw * 64;
     if (iv.nseg == 0)
         return;
@@ -382,6 +415,16 @@ __device__ __forceinline__ void mark(uint32_t* bm32, uint32_t pos)
     __hip_atomic_fetch_or(w, 1u << (pos & 31), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// Column layout: set the bit of the position whose log2R bits are the top of
+// P (the bits below are ignored): the top five are the bit, the rest the word.
+template <int LR>
+__device__ __forceinline__ void mark_col(uint32_t P)
+{
+    const uint32_t a = (P >> (30 - LR)) & (((1u << (LR - 5)) - 1) << 2);
+    typedef __attribute__((address_space(3))) uint32_t lds_u32;
+    __hip_atomic_fetch_or((lds_u32*)(uintptr_t)a + kColGuard, 1u << (P >> 27), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
 // Store bytes [b0, b1) of the 16 bytes v at the 16-byte aligned p (b0, b1
 // wave-uniform): whole dwords as dwords, the rest byte by byte.
 __device__ __forceinline__ void store_part16(g_u8* p, const u32x4 v, uint32_t b0, uint32_t b1)
@@ -482,7 +525,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
     extern __shared__ uint64_t lds[];
 
     const uint32_t tid = threadIdx.x, T = blockDim.x, lane = tid & 63u;
-    const uint32_t S = 1u << L.log2S, SW = S >> 6;
+    const uint32_t S = L.S, SW = S >> 6;
     const uint32_t R = L.rw * 64;
     const uint32_t HW = L.hlo_words;
     const uint32_t nmed = L.med_end - kFirstMedium;
@@ -696,12 +739,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
         auto first_hits = [&](int64_t B1, bool restart, uint32_t lid, uint32_t nl) {
             if (restart) {
                 for (uint32_t i = lid; i < nmed; i += nl) {
-                    const uint32_t q = s_medq[i].x;
-                    const int64_t d = (int64_t)((q - 1) >> 1) - B1;
-                    int64_t f = d % (int64_t)q;
-                    if (f < 0)
-                        f += q;
-                    s_f[i] = (uint32_t)f;
+                    s_f[i] = (uint32_t)first_hit_b(B1, s_medq[i].x, L.qinv[kFirstMedium + i]);
                 }
             } else {
                 for (uint32_t i = lid; i < nmed; i += nl) {
@@ -1202,10 +1240,542 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
     }
 }
 
+// Run `it` of a launch over one interval of ns segments: the first `grid` runs
+// are run_long segments each, the rest of the segments is cut into runs of
+// run_short; or, with run_long = 0, n_items equal runs.
+__device__ __forceinline__ void run_of(uint32_t it, uint32_t ns, uint32_t n_items, uint32_t run_long,
+                                       uint32_t run_short, uint32_t grid, uint32_t* first, uint32_t* n)
+{
+    if (run_long == 0) {
+        *first = (uint32_t)((uint64_t)it * ns / n_items);
+        *n = (uint32_t)((uint64_t)(it + 1) * ns / n_items) - *first;
+    } else if (it < grid) {
+        *first = it * run_long;
+        *n = run_long;
+    } else {
+        *first = grid * run_long + (it - grid) * run_short;
+        *n = min(run_short, ns - *first);
+    }
+}
+
+// Summary mode in the column layout (see esq_internal.h): regions of 2^kColLog2
+// bits by workgroups of kColBlock threads, four of them on a CU.
+//
+// What bounds it: the issue of vector instructions and the waits between them.
+// Per 64-n word the row layout's summary form issues 65 vector instructions
+// (30 in the search, a third of them half-rate funnel shifts) and 45 scalar
+// ones; here it is 42 and 17, of which the search has 23 (8 popcounts, 8
+// ANDs).  The vector units are busy for about 0.6 of the time, the LDS for
+// 0.47; the rest are barriers and latencies of eight waves a SIMD, which is
+// why block size, region length and trip counts are constants and the rare
+// paths (first segments, deep n) have loops of their own: with runtime trip
+// counts and the offers in the common path the same method took 204 us.
+// On the 2^33 odd n below 2^50: 221 us in the row layout, 174 us here (4.9e13
+// n/s); a third table for 17 and 19 took 184, regions of 2^19 211, of 2^17
+// 203.
+template <bool PH>
+__global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_column(Launch Larg)
+{
+    constexpr int LR = kColLog2;
+    constexpr uint32_t T = kColBlock;
+    extern __shared__ uint64_t lds[];  // at LDS address 0
+    constexpr uint32_t R = 1u << LR, W = R / 32, H = kColHalo, S = R - H;
+    static_assert(H <= W && H % 256 == 0, "the halo lies in the lowest bit of the region's words");
+    constexpr uint32_t kS1 = S % kWheelPeriod, kS2 = S % kWheel2Period;
+    // The launch's and the interval's fields are read from memory (scalar
+    // loads) where they are used, through pointers that the compiler takes to
+    // change from segment to segment: kept in registers they do not fit, and
+    // spilled scalars cost a vector instruction each.
+    typedef const __attribute__((address_space(4))) Launch CLaunch;
+    typedef const __attribute__((address_space(4))) Interval CInterval;
+    CLaunch* lp = (CLaunch*)__builtin_amdgcn_kernarg_segment_ptr();
+    (void)Larg;
+
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = rfl(tid >> 6);
+    // kColGuard words, then the region's W; the words below word 0 wrap (the
+    // whole-segment search's reads of them are the guard's)
+    uint32_t* bm = reinterpret_cast<uint32_t*>(lds) + kColGuard;
+    constexpr uint32_t kRw = (W + kColGuard) / 2;
+    constexpr uint32_t kCntAt = kMaxKh + 2, kItemAt = kCntAt + (kMaxKh + 2) / 2, kPhAt = kItemAt + 2;
+    static_assert(kPhAt + 3 <= kVerifyCtrlWords, "control block");
+    unsigned long long* s_first = reinterpret_cast<unsigned long long*>(lds + kRw);  // kMaxKh + 2
+    uint32_t* s_cnt = reinterpret_cast<uint32_t*>(lds + kRw + kCntAt);               // kMaxKh + 1
+    uint32_t* s_item = reinterpret_cast<uint32_t*>(lds + kRw + kItemAt);             // 4
+    unsigned long long* s_ph = reinterpret_cast<unsigned long long*>(lds + kRw + kPhAt);
+    uint2* s_medq = reinterpret_cast<uint2*>(lds + kRw + kVerifyCtrlWords);
+    const uint32_t nmed = lp->med_end - kFirstMedium, n_multi = lp->n_multi;
+    uint32_t* s_f = reinterpret_cast<uint32_t*>(s_medq + nmed);
+    for (uint32_t i = tid; i < nmed; i += T)
+        s_medq[i] = lp->medq[i];
+    // a lane's first task is its own for the whole launch
+    uint2 task = {0u, 0u};
+    uint32_t task_min = 0;
+    if (tid < lp->n_tasks) {
+        task = lp->tasks[tid];
+        task_min = lp->task_min[wave];
+    }
+    task_min = rfl(task_min);
+    const uint32_t n_tasks = lp->n_tasks, cap = lp->bucket_cap;
+    const uint32_t* const bcnt = lp->bucket_cnt;
+    const uint32_t* const bslot = lp->bucket_slot;
+    const uint32_t* const col = lp->col;
+
+    constexpr int kRegLevels = 5;
+    uint32_t cnt[kRegLevels + 1];
+    uint32_t found = 0;       // levels whose least n this run has already offered
+    uint32_t cur_iv = ~0u, acc_segs = 0;
+    auto flush = [&](uint32_t iv) {
+        asm volatile("" : "+s"(lp));
+        Acc* acc = lp->iv[iv].acc;
+        const uint32_t klds = lp->k_lds;
+#pragma unroll
+        for (int k = 1; k <= kRegLevels; k++) {
+            uint32_t v = cnt[k];
+            for (int o = 32; o > 0; o >>= 1)
+                v += __shfl_xor(v, o);
+            if (lane == 0 && v)
+                atomicAdd(&s_cnt[k], v);
+        }
+        __syncthreads();
+        if (tid >= 1 && tid <= klds && s_cnt[tid])
+            g_add(&acc->cnt[tid], (unsigned long long)s_cnt[tid]);
+        if (tid >= 2 && tid <= klds + 1 && s_first[tid] != kNone)
+            g_min(&acc->first[tid], s_first[tid]);
+        __syncthreads();
+    };
+    uint64_t t_ph = 0;
+    if (PH && tid < 3)
+        s_ph[tid] = 0;
+    auto phase_tick = [&](int ph) {
+        if (PH) {
+            const uint64_t t = __builtin_amdgcn_s_memrealtime();
+            if (ph >= 0 && tid == 0)
+                atomicAdd(&s_ph[ph], (unsigned long long)(t - t_ph));
+            t_ph = t;
+        }
+    };
+    // Work items.  The first is the workgroup's own number; the others come
+    // from the queue, fetched before the last segment's search (thread 0).  A
+    // thousand workgroups taking their first item from one counter waited up
+    // to 14 us for it.
+    uint32_t item = blockIdx.x;
+    for (;;) {
+        asm volatile("" : "+s"(lp));
+        if (tid == 0) {
+            uint32_t ok = 0, ivi = 0, b = 0, n = 0;
+            const uint32_t it = item;
+            if (it < lp->n_items) {
+                ok = 1;
+                if (lp->items) {
+                    const uint4 x = lp->items[it];
+                    ivi = x.x;
+                    b = x.y;
+                    n = x.z;
+                } else {
+                    run_of(it, lp->iv[0].nseg, lp->n_items, lp->run_long, lp->run_short, gridDim.x, &b, &n);
+                }
+            }
+            s_item[0] = ivi;
+            s_item[1] = b;
+            s_item[2] = n;
+            s_item[3] = ok;
+        }
+        __syncthreads();
+        const uint32_t item_ok = rfl(s_item[3]);
+        const uint32_t ivi = rfl(s_item[0]), seg0 = rfl(s_item[1]), nsegs = rfl(s_item[2]);
+        // partial totals go out as in k_verify
+        if (cur_iv != ~0u && (!item_ok || ivi != cur_iv || acc_segs + nsegs > kFlushSegs)) {
+            flush(cur_iv);
+            cur_iv = ~0u;
+        }
+        if (!item_ok) {
+            if (PH && tid < 3)
+                atomicAdd(&lp->phase[tid], s_ph[tid]);
+            break;
+        }
+        if (cur_iv == ~0u) {
+            if (tid < kMaxKh + 2)
+                s_first[tid] = kNone;
+            if (tid <= kMaxKh)
+                s_cnt[tid] = 0;
+#pragma unroll
+            for (int k = 0; k <= kRegLevels; k++)
+                cnt[k] = 0;
+            found = 0;
+            acc_segs = 0;
+            cur_iv = ivi;
+            __syncthreads();
+        }
+        acc_segs += nsegs;
+        CInterval* ivp = (CInterval*)(uintptr_t)(lp->iv + ivi);
+        // n-index of region position 0's slot: slot y is n-index nh + y, its
+        // k-th candidate position y - (2^(k-1) - 1), position 0 odd index nh - 1
+        int64_t nh = ivp->A0 + (int64_t)seg0 * (int64_t)S - (int64_t)H;
+        const uint64_t I1 = ivp->I1;
+        // the region's first word in each table, carried along
+        uint32_t x1, x2;
+        {
+            auto fmod = [](int64_t x, int64_t m) {
+                const int64_t r = x % m;
+                return rfl((uint32_t)(r < 0 ? r + m : r));
+            };
+            x1 = fmod(nh - 1, kWheelPeriod);
+            x2 = fmod(nh - 1, kWheel2Period);
+        }
+        // Hit slots.  Lane l holds the counts of the run's segments l, l + 64,
+        // ... in turn: a scalar load of each segment's own count would be
+        // waited for by the next LDS read.  This lane's first slot is fetched
+        // a segment ahead, after the marks: vector loads complete in order,
+        // and the next one that is waited for is then a whole search away.
+        uint32_t gs = ivp->seg_base + seg0, n_seg = 0;  // n_seg: segments of the run done
+        auto slot_counts = [&](uint32_t done) {
+            return bcnt && done + lane < nsegs ? bcnt[gs + lane] : 0u;
+        };
+        auto slot_of = [&](uint32_t g, uint32_t n) {
+            return tid < min(n, cap) ? bslot[(uint64_t)g * cap + tid] : R;
+        };
+        uint32_t counts = slot_counts(0);
+        uint32_t nb = rfl(counts);
+        uint32_t slot_pos = slot_of(gs, nb);
+        for (uint32_t left = nsegs; left > 0; left--, nh += S) {
+            asm volatile("" : "+s"(lp), "+s"(ivp));
+            phase_tick(-1);
+            // 1. the two tables, four words per lane and load
+            {
+                const char* src1 = reinterpret_cast<const char*>(col + x1);
+                const char* src2 = reinterpret_cast<const char*>(col + (kWheelPeriod + W) + x2);
+                char* dst = reinterpret_cast<char*>(bm);
+                uint32_t off = 16 * tid;
+                asm volatile("" : "+v"(off));
+                constexpr int kQuads = W / (4 * T), kU = 2;  // kU quads in flight (VGPR budget)
+                static_assert(W % (4 * T * kU) == 0, "whole rounds of quads");
+#pragma unroll
+                for (int r = 0; r < kQuads; r += kU) {
+                    u32x4 v[kU], x[kU];
+#pragma unroll
+                    for (int u = 0; u < kU; u++) {
+                        v[u] = *reinterpret_cast<const u32x4u*>(src1 + off + (r + u) * (16 * T));
+                        x[u] = *reinterpret_cast<const u32x4u*>(src2 + off + (r + u) * (16 * T));
+                    }
+#pragma unroll
+                    for (int u = 0; u < kU; u++)
+                        *reinterpret_cast<u32x4*>(dst + off + (r + u) * (16 * T)) = v[u] | x[u];
+                }
+                x1 = x1 + kS1 >= kWheelPeriod ? x1 + kS1 - kWheelPeriod : x1 + kS1;
+                x2 = x2 + kS2 >= kWheel2Period ? x2 + kS2 - kWheel2Period : x2 + kS2;
+            }
+            // the medium primes' first hits in a run's first segment (carried
+            // from segment to segment after that, see below)
+            if (left == nsegs) {
+                for (uint32_t i = tid; i < nmed; i += T)
+                    s_f[i] = (uint32_t)first_hit_b(nh - 1, s_medq[i].x, lp->qinv[kFirstMedium + i]);
+            }
+            __syncthreads();
+            phase_tick(0);
+
+            // 2. odd multiples of p^2.  A position is carried with its LR bits
+            //    at the top of a word: stepping past the region is the add's
+            //    carry, and the mark's bit is the top five.  The bit set below
+            //    the position makes the step 2^32 - 1 (no shorter than the
+            //    region) carry from position 0 too.
+            if (nh < 1)  // odd indices below 0 are not positive
+                for (uint32_t i = tid; i < (uint32_t)(1 - nh); i += T)
+                    mark_col<LR>(i << (32 - LR));
+            {
+                // tasks: the marks that every task of the wave makes in a
+                // loop without a test, the rest one by one
+                auto run_task = [&](const uint2 tk, uint32_t n) {
+                    const uint32_t pos = s_f[tk.x >> 21] + (tk.x & 0x1fffffu), step = tk.y;
+                    uint32_t P = (pos << (32 - LR)) | 1u;
+                    bool out = pos >= R;
+                    if (n) {
+#pragma unroll 4
+                        for (uint32_t t = 1; t < n; t++) {
+                            mark_col<LR>(P);
+                            P += step;
+                        }
+                        mark_col<LR>(P);
+                        P += step;
+                        out = P < step;
+                    }
+                    while (!out) {
+                        mark_col<LR>(P);
+                        P += step;
+                        out = P < step;
+                    }
+                };
+                if (tid < n_tasks)
+                    run_task(task, task_min);
+                for (uint32_t e = tid + T; e < n_tasks; e += T)
+                    run_task(lp->tasks[e], rfl(lp->task_min[e >> 6]));
+                // the other medium primes, at most entry_hits marks each, by
+                // the lanes in reverse, away from the longest tasks
+                for (uint32_t i = n_multi + (T - 1 - tid); i < nmed; i += T) {
+                    const uint2 qs = s_medq[i];
+                    const uint32_t f = s_f[i];
+                    s_f[i] = f >= qs.y ? f - qs.y : f + qs.x - qs.y;  // in the next segment
+                    if (f < R) {
+                        uint32_t P = (f << (32 - LR)) | 1u;
+                        const uint32_t step = qs.x >= R ? ~0u : qs.x << (32 - LR);
+                        do {
+                            mark_col<LR>(P);
+                            P += step;
+                        } while (P >= step);
+                    }
+                }
+            }
+            if (nb <= cap) {
+                if (slot_pos < R)
+                    mark_col<LR>(slot_pos << (32 - LR));
+                for (uint32_t e = tid + T; e < nb; e += T) {
+                    const uint32_t pos = bslot[(uint64_t)gs * cap + e];
+                    if (pos < R)
+                        mark_col<LR>(pos << (32 - LR));
+                }
+            } else {
+                // slots overflowed: every prime above the medium range, directly
+                for (uint32_t pi = lp->med_end + tid; pi < ivp->pmax_end; pi += T) {
+                    const uint64_t p = lp->primes[pi];
+                    const uint64_t q = p * p;
+                    for (uint64_t pos = first_hit(nh - 1, q); pos < R; pos += q)
+                        mark_col<LR>((uint32_t)pos << (32 - LR));
+                }
+            }
+            __syncthreads();
+            phase_tick(1);
+            gs++;
+            n_seg++;
+            if ((n_seg & 63u) == 0)
+                counts = slot_counts(n_seg);
+            nb = n_seg < nsegs ? (uint32_t)__builtin_amdgcn_readlane((int)counts, (int)(n_seg & 63u)) : 0u;
+            slot_pos = slot_of(gs, nb);
+            // the next first hits of the primes with tasks, by a wave that has
+            // less to do in the search than others
+            if (wave == 1)
+                for (uint32_t i = lane; i < n_multi; i += 64) {
+                    const uint2 qs = s_medq[i];
+                    const uint32_t f = s_f[i];
+                    s_f[i] = f >= qs.y ? f - qs.y : f + qs.x - qs.y;
+                }
+            if (left == 1 && tid == 0)
+                item = lp->n_items > gridDim.x ? gridDim.x + atomicAdd(lp->queue, 1u) : ~0u;
+
+            // 3. Algorithm 2.  The n of the segment are the slots [H, yhi).
+            const uint32_t yhi = (uint32_t)min((uint64_t)R, I1 - (uint64_t)nh);
+            found = rfl(found);
+            // least n of depth 2, 3, 4: the slots in order, one wave per level;
+            // a level found in an earlier segment of the run has its least n there
+            if ((found & 0x1cu) != 0x1cu) {
+                for (uint32_t k = 1; k <= 3; k++) {
+                    if ((found & (2u << k)) || k - 1 != wave)
+                        continue;
+                    constexpr int kAhead = 4;  // words of 64 slots in flight
+                    for (uint32_t y0 = H; y0 < yhi; y0 += 64 * kAhead) {
+                        auto bit = [&](uint32_t p) { return bm[p & (W - 1)] >> ((p >> (LR - 5)) & 31u); };
+                        uint32_t u[kAhead];
+#pragma unroll
+                        for (int j = 0; j < kAhead; j++) {
+                            const uint32_t y = y0 + 64 * j + lane;
+                            u[j] = y < yhi ? bit(y) : 0u;
+                            if (k > 1)
+                                u[j] &= bit(y - 1);
+                            if (k > 2)
+                                u[j] &= bit(y - 3);
+                        }
+                        uint32_t at = ~0u;
+#pragma unroll
+                        for (int j = kAhead - 1; j >= 0; j--) {
+                            const uint64_t bal = __ballot((u[j] & 1u) != 0);
+                            if (bal)
+                                at = y0 + 64 * j + (uint32_t)(__ffsll((unsigned long long)bal) - 1);
+                        }
+                        if (at != ~0u) {
+                            if (lane == 0)
+                                atomicMin(&s_first[k + 1], (unsigned long long)nh + at);
+                            break;
+                        }
+                    }
+                }
+            }
+            // word i of the region for any i > -W: below 0, word W + i one bit up
+            auto word_at = [&](int32_t i) { return bm[(uint32_t)i & (W - 1)] << (i < 0 ? 1 : 0); };
+            auto n_of = [&](uint32_t i, uint32_t u) {  // n-index of the least slot in u of word i
+                return (unsigned long long)nh + (((uint32_t)__ffs((int)u) - 1u) << (LR - 5)) + i;
+            };
+            // offer the least n in the four words from i0 as least n of depth d;
+            // few lanes have any, so each does its own LDS operation (the
+            // address is kept from looking uniform, which would make it a
+            // reduction over the wave first)
+            auto offer = [&](uint32_t d, uint32_t i0, const uint32_t (&u)[4]) {
+                unsigned long long at = kNone;
+#pragma unroll
+                for (uint32_t c = 0; c < 4; c++)
+                    if (u[c])
+                        at = min(at, n_of(i0 + c, u[c]));
+                asm volatile("" : "+v"(d));
+                if (at != kNone)
+                    atomicMin(&s_first[d], at);
+            };
+            // Four words per lane.  KIND 0: every slot of the wave's 256 words
+            // is an n of the segment; 1: all but those in bit 0 (words below 0
+            // from the guard); 2: the general form, which also wraps below
+            // word 0 and offers levels 5 and 6.
+            auto quad_pass = [&](auto kind_c, uint32_t i0) {
+                constexpr int KIND = decltype(kind_c)::value;
+                auto quad = [&](int32_t i) {
+                    if (KIND == 2)
+                        return *reinterpret_cast<const u32x4*>(bm + ((uint32_t)i & (W - 1))) << (i < 0 ? 1u : 0u);
+                    return *reinterpret_cast<const u32x4*>(bm + i);
+                };
+                const u32x4 wc = quad((int32_t)i0), wb = quad((int32_t)i0 - 4), wa = quad((int32_t)i0 - 8);
+                // words i0 - 15 .. i0 - 12 (one unaligned read of them costs
+                // four times the LDS cycles)
+                const u32x4 za = quad((int32_t)i0 - 16), zb = quad((int32_t)i0 - 12);
+                const uint32_t wz[4] = {za[1], za[2], za[3], zb[0]};
+                const uint32_t w[12] = {wa[0], wa[1], wa[2], wa[3], wb[0], wb[1], wb[2], wb[3],
+                                        wc[0], wc[1], wc[2], wc[3]};
+                uint32_t u[4];
+#pragma unroll
+                for (int c = 0; c < 4; c++) {
+                    uint32_t U = w[8 + c];
+                    if (KIND == 1)
+                        U &= ~1u;
+                    if (KIND == 2) {
+                        // bits j with H <= j W + i < yhi
+                        const uint32_t i = i0 + (uint32_t)c;
+                        const uint32_t jh = (yhi + W - 1 - i) >> (LR - 5);
+                        U &= (jh >= 32 ? ~0u : (1u << jh) - 1u) & (i < H ? ~1u : ~0u);
+                    }
+                    cnt[1] = bcnt_acc(U, cnt[1]);
+                    U &= w[7 + c];
+                    cnt[2] = bcnt_acc(U, cnt[2]);
+                    U &= w[5 + c];
+                    cnt[3] = bcnt_acc(U, cnt[3]);
+                    U &= w[1 + c];
+                    cnt[4] = bcnt_acc(U, cnt[4]);
+                    u[c] = U;
+                }
+                if (KIND == 2 && !(found & (1u << 5)))
+                    offer(5, i0, u);
+#pragma unroll
+                for (int c = 0; c < 4; c++)
+                    u[c] &= wz[c];
+                // of 8192 n 1.2 are left after step 4 and 0.08 after step 5:
+                // the first test for an empty wave pays here (at step 4 it
+                // saves three tenths of the waves six instructions)
+                if (__builtin_expect(__ballot((u[0] | u[1] | u[2] | u[3]) != 0) == 0, 1))
+                    return;
+#pragma unroll
+                for (int c = 0; c < 4; c++)
+                    cnt[5] = bcnt_acc(u[c], cnt[5]);
+                if (KIND == 2 && !(found & (1u << 6)))
+                    offer(6, i0, u);
+                const uint32_t klds = lp->k_lds;
+                uint32_t k = 5;
+                if (klds > 5) {
+                    // step 6, which leaves next to none, for the four words at once
+                    const u32x4 ya = quad((int32_t)i0 - 32), yb = quad((int32_t)i0 - 28);
+                    u[0] &= ya[1];
+                    u[1] &= ya[2];
+                    u[2] &= ya[3];
+                    u[3] &= yb[0];
+                    k = 6;
+                    if (__ballot((u[0] | u[1] | u[2] | u[3]) != 0) == 0)
+                        return;
+                    const uint32_t c6 = (uint32_t)(__popc(u[0]) + __popc(u[1]) + __popc(u[2]) + __popc(u[3]));
+                    if (c6)
+                        atomicAdd(&s_cnt[6], c6);
+                    offer(7, i0, u);
+                }
+#pragma nounroll
+                for (uint32_t c = 0; c < 4; c++) {
+                    uint32_t U = c == 0 ? u[0] : c == 1 ? u[1] : c == 2 ? u[2] : u[3];
+                    for (uint32_t kk = k; U && kk < klds;) {
+                        kk++;
+                        U &= word_at((int32_t)(i0 + c) - (int32_t)((1u << (kk - 1)) - 1u));
+                        if (U) {
+                            // U: the slots of depth > kk
+                            atomicAdd(&s_cnt[kk], (uint32_t)__popc(U));
+                            atomicMin(&s_first[kk + 1], n_of(i0 + c, U));
+                        }
+                    }
+                    // still unresolved: to the tail pass or the exceptions, as in k_verify
+                    if (__builtin_expect(U != 0, 0) && (klds < lp->kmax_eff || lp->exc_list)) {
+                        const unsigned long long cu = (unsigned long long)__popc(U);
+                        g_add(&ivp->acc->tail_count, cu);
+                        unsigned long long idx = atomicAdd(lp->tail_count, cu);
+                        for (uint32_t x = U; x; x &= x - 1, idx++) {
+                            if (idx < lp->tail_cap) {
+                                lp->tail_n[idx] = n_of(i0 + c, x);
+                                lp->tail_iv[idx] = ivi;
+                            } else {
+                                g_or(&ivp->acc->status, klds >= lp->kmax_eff
+                                                            ? (unsigned)ESQ_STATUS_EXCEPTIONS_INCOMPLETE
+                                                            : (unsigned)ESQ_STATUS_TAIL_OVERFLOW);
+                            }
+                        }
+                    }
+                }
+            };
+            constexpr uint32_t kStep = 4 * T;  // words per round of quads
+            // opaque, so that no addresses are kept from segment to segment
+            uint32_t t4 = 4 * tid;
+            asm volatile("" : "+v"(t4));
+            if (yhi == R && (found & 0x60u) == 0x60u) {
+                // a whole segment, the levels up to 6 offered
+                if (wave == 0 && lane < kColGuard)  // only this wave reads the guard
+                    bm[(int32_t)lane - (int32_t)kColGuard] = bm[W - kColGuard + lane] << 1;
+#pragma unroll
+                for (uint32_t a = 0; a < W; a += kStep) {
+                    const uint32_t i0 = a + t4;
+                    if (a < H)
+                        quad_pass(std::integral_constant<int, 1>{}, i0);
+                    else
+                        quad_pass(std::integral_constant<int, 0>{}, i0);
+                }
+                static_assert(H % kStep == 0 || H == W, "a round's words lie on one side of H");
+            } else {
+#pragma nounroll
+                for (uint32_t i0 = t4; i0 < W; i0 += kStep)
+                    quad_pass(std::integral_constant<int, 2>{}, i0);
+            }
+            __syncthreads();
+            // the levels found by now need no offers in later segments
+            if ((found & 0x7cu) != 0x7cu) {
+                uint32_t fnd = 0;
+#pragma unroll
+                for (int k = 2; k <= 6; k++)
+                    fnd |= s_first[k] != kNone ? 1u << k : 0u;
+                found = rfl(fnd);
+            }
+            phase_tick(2);
+        }
+        // the item's s_item slots are reused by the next fetch
+        __syncthreads();
+    }
+}
+
+
 size_t verify_lds_bytes(const Launch& L, uint32_t block)
 {
-    return verify_lds_size(L.rw, L.med_end - kFirstMedium, L.tasks_in_lds ? L.n_tasks : 0u, L.stage != 0,
+    return verify_lds_size(L.rw + (L.mode == 3 ? kColGuard / 2 : 0u), L.med_end - kFirstMedium, L.tasks_in_lds ? L.n_tasks : 0u, L.stage != 0,
                            block);
+}
+
+// The instance of a mode; the phase-clock ones only when the clock is on.
+using VerifyKernel = void (*)(Launch);
+static VerifyKernel verify_kernel(int mode, bool phase)
+{
+    switch (mode) {
+    case 0:
+        return phase ? k_verify<0, true> : k_verify<0, false>;
+    case 1:
+        return phase ? k_verify<1, true> : k_verify<1, false>;
+    case 2:
+        return phase ? k_verify<2, true> : k_verify<2, false>;
+    default:
+        return phase ? k_column<true> : k_column<false>;
+    }
 }
 
 hipError_t launch_verify(const Launch& L, uint32_t grid, uint32_t block, hipStream_t s)
@@ -1213,43 +1783,17 @@ hipError_t launch_verify(const Launch& L, uint32_t grid, uint32_t block, hipStre
     const size_t lds = verify_lds_bytes(L, block);
     if (grid == 0 || L.n_items == 0)
         return hipSuccess;
-    // the phase-clock instances only when the clock is on
-    switch (L.mode * 2 + (L.phase ? 1 : 0)) {
-    case 0:
-        hipLaunchKernelGGL((k_verify<0, false>), dim3(grid), dim3(block), lds, s, L);
-        break;
-    case 1:
-        hipLaunchKernelGGL((k_verify<0, true>), dim3(grid), dim3(block), lds, s, L);
-        break;
-    case 2:
-        hipLaunchKernelGGL((k_verify<1, false>), dim3(grid), dim3(block), lds, s, L);
-        break;
-    case 3:
-        hipLaunchKernelGGL((k_verify<1, true>), dim3(grid), dim3(block), lds, s, L);
-        break;
-    case 4:
-        hipLaunchKernelGGL((k_verify<2, false>), dim3(grid), dim3(block), lds, s, L);
-        break;
-    default:
-        hipLaunchKernelGGL((k_verify<2, true>), dim3(grid), dim3(block), lds, s, L);
-        break;
-    }
+    hipLaunchKernelGGL(verify_kernel((int)L.mode, L.phase != nullptr), dim3(grid), dim3(block), lds, s, L);
     return hipGetLastError();
 }
 
 int verify_occupancy(int mode, uint32_t block, size_t lds_bytes)
 {
     int occ = 0;
-    hipError_t e;
-    if (mode == 1)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_verify<1>, (int)block, lds_bytes);
-    else
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_verify<0>, (int)block, lds_bytes);
-    if (e != hipSuccess)
-        return 1;
-    return occ > 0 ? occ : 1;
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &occ, reinterpret_cast<const void*>(verify_kernel(mode, false)), (int)block, lds_bytes);
+    return e == hipSuccess && occ > 0 ? occ : 1;
 }
-
 
 // --------------------------------------------------------------- tail
 
@@ -1493,13 +2037,12 @@ hipError_t configure_kernels()
 {
     hipError_t e;
     const int lds_max = (int)kVerifyLdsMax;
-    const void* fns[6] = {(const void*)k_verify<0, false>, (const void*)k_verify<0, true>,
-                          (const void*)k_verify<1, false>, (const void*)k_verify<1, true>,
-                          (const void*)k_verify<2, false>, (const void*)k_verify<2, true>};
-    for (const void* f : fns) {
-        e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
-        if (e != hipSuccess) return e;
-    }
+    for (int mode = 0; mode < 4; mode++)
+        for (int phase = 0; phase < 2; phase++) {
+            e = hipFuncSetAttribute(reinterpret_cast<const void*>(verify_kernel(mode, phase != 0)),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, lds_max);
+            if (e != hipSuccess) return e;
+        }
     e = hipFuncSetAttribute((const void*)k_finalize, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)(kFinalizeSortCap * 8));
     return e;
