@@ -96,8 +96,7 @@ struct Ctx {
     uint64_t plimit = 0;            // every odd prime <= plimit is in `primes`
     std::vector<uint32_t> primes;   // odd primes ascending (3, 5, 7, ...)
     std::vector<double> inv_pref;   // inv_pref[i] = sum over t < i of 1 / primes[t]^2
-    uint32_t* d_primes = nullptr;   // the primes, their coarse index, Barrett reciprocals
-    uint32_t pidx_n = 0;
+    uint32_t* d_primes = nullptr;   // the primes, the bitmap of odd primes, Barrett reciprocals
     size_t qinv_at = 0;             // offset (uint32 units) of the reciprocals in d_primes
     uint32_t n_qinv = 0;            // primes[0 .. n_qinv) have one
     uint64_t* d_wheel = nullptr;
@@ -507,6 +506,13 @@ int prebuild_med_table(Ctx* c, const Params& par)
     return ESQ_OK;
 }
 
+// Launches with at least so many hits of large primes expected have
+// k_bucket_own find them (see there): below it, k_bucket's counters in memory
+// see few enough hits, and its primes spread over more of the chip (10^8 odd n,
+// 3e3 hits: 6.7 us, 10.6 with k_bucket_own; 2^31, 6e4 hits: 11.8 and 9.5; 1024
+// intervals, 9e5 hits: 110 and 63).
+constexpr double kOwnMinHits = 4e4;
+
 // One interval to process, in odd-index terms: verify -> the n-indices
 // [I0, I1); sieve -> the m-indices of the output bits.
 struct Req {
@@ -521,10 +527,14 @@ struct Planned {
     int mode = 0;
     std::vector<Interval> ivs;
     std::vector<uint4> items;
-    uint32_t n_heavy = 0, max_direct = 0, max_cof = 0, grid = 0, block = 256;
+    std::vector<uint4> ranges;  // k_bucket_own, several intervals: (interval, first segment, segments, 0)
+    uint32_t n_ranges = 0;      // its workgroups; 0: k_bucket
+    char* base = nullptr;       // the scratch it is bound to
+    uint32_t n_heavy = 0, max_direct = 0, max_cof = 0, p_cof = 0, grid = 0, block = 256;
+    bool in_doubles = false;
     bool any_bucket = false;
     uint64_t nseg_total = 0;
-    size_t bytes = 0, o_iv = 0, o_acc = 0, o_items = 0, o_bcnt = 0, o_bslot = 0, o_misc = 0;
+    size_t bytes = 0, o_iv = 0, o_acc = 0, o_items = 0, o_bcnt = 0, o_bslot = 0, o_misc = 0, o_ranges = 0;
     size_t o_tn = 0, o_tiv = 0, o_td = 0;
 };
 
@@ -607,7 +617,10 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     uint64_t P0 = kCofactorPrime;
     const uint64_t direct_threads_full =
         (uint64_t)n_live * (uint64_t)(std::max(med_end, prime_upper(c, kCofactorPrime)) - med_end);
-    if (direct_threads_full > (uint64_t)c->n_cu * 2048) {
+    const uint32_t all_end = std::max(med_end, prime_upper(c, pmax_all));
+    const bool own = all_end > med_end && (double)nseg_total * (double)R *
+                                              (c->inv_pref[all_end] - c->inv_pref[med_end]) >= kOwnMinHits;
+    if (own || direct_threads_full > (uint64_t)c->n_cu * 2048) {
         double best = 0;
         for (int h = 20; h <= 40; h++) {
             const uint64_t cand = (uint64_t)std::ldexp(1.0, h / 2) * (h % 2 ? 1.41421356 : 1.0);
@@ -643,6 +656,9 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
             // cofactor j's range holds about L / (2 sqrt(m j) ln p) primes:
             // the j with more than 4 share them over 8 lanes
             const double m_lo = std::max(1.0, 2.0 * (double)B0 + 1);
+            v.sqrt_lo = std::sqrt(m_lo);
+            v.sqrt_hi = std::sqrt((double)m_hi);
+            P->p_cof = (uint32_t)pc;  // the same for every interval that has cofactors
             const double span = 2.0 * (double)E;
             const double per_j = span / (2.0 * std::sqrt(m_lo) * std::log((double)pc));
             const double j_wide = (per_j / 4.0) * (per_j / 4.0);
@@ -654,7 +670,30 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
         max_cof = std::max(max_cof, v.n_cof + 7 * v.n_cof_wide);  // cofactor threads
         E_max = std::max(E_max, (uint64_t)(v.nseg - 1) * S + R);
     }
-    // bucket primes with more than 8 hits in the longest interval get a
+    // Workgroups of k_bucket_own: one per CU where the intervals allow, each
+    // with an even share of one interval's segments (two per CU: 2^33 odd n
+    // 26 us, one: 19).
+    P->ranges.clear();
+    P->n_ranges = 0;
+    if (any_bucket && own) {
+        const uint64_t wanted = (uint64_t)c->n_cu;
+        const uint64_t share = std::min<uint64_t>(kOwnSegs, (nseg_total + wanted - 1) / wanted);
+        uint64_t n_ranges = 0;
+        for (uint32_t i = 0; i < n_iv; i++) {
+            const uint64_t parts = (ivs[i].nseg + share - 1) / share;
+            n_ranges += parts;
+            for (uint64_t k = 0; k < parts && n_iv > 1; k++) {
+                uint4 r;
+                r.x = i;
+                r.y = (uint32_t)(k * ivs[i].nseg / parts);
+                r.z = (uint32_t)((k + 1) * ivs[i].nseg / parts) - r.y;
+                r.w = 0;
+                P->ranges.push_back(r);
+            }
+        }
+        P->n_ranges = (uint32_t)n_ranges;
+    }
+    // k_bucket: primes with more than 8 hits in the longest interval get a
     // group of lanes each
     uint32_t n_heavy = 0;
     if (any_bucket) {
@@ -769,6 +808,8 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     off = align_up(off + sizeof(Acc) * std::max<uint32_t>(n_iv, 1));
     P->o_items = off;
     off = align_up(off + sizeof(uint4) * items.size());
+    P->o_ranges = off;
+    off = align_up(off + sizeof(uint4) * P->ranges.size());
     P->o_bcnt = off;
     off = align_up(off + (any_bucket ? nseg_total * 4 : 0));
     P->o_bslot = off;
@@ -810,8 +851,8 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     L.bucket_cap = cap;
     L.nprimes = (uint32_t)c->primes.size();
     L.primes = c->d_primes;
-    L.pidx = c->d_primes + c->primes.size();
-    L.pidx_n = c->pidx_n;
+    L.pbits = c->d_primes + c->primes.size();
+    L.plimit = (uint32_t)c->plimit;
     L.qinv = reinterpret_cast<const uint64_t*>(c->d_primes + c->qinv_at);
     L.n_qinv = c->n_qinv;
     L.medq = mt ? mt->medq : nullptr;
@@ -832,6 +873,7 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     P->n_heavy = n_heavy;
     P->max_direct = max_direct;
     P->max_cof = max_cof;
+    P->in_doubles = m_hi_max < (1ull << 53);  // odd indices below 2^52 in doubles
     P->any_bucket = any_bucket;
     P->nseg_total = nseg_total;
     P->grid = (uint32_t)std::min<uint64_t>(n_items, resident);
@@ -843,6 +885,7 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
 void bind(Planned* P, char* base)
 {
     Launch& L = P->L;
+    P->base = base;
     Acc* accs = (Acc*)(base + P->o_acc);
     for (size_t i = 0; i < P->ivs.size(); i++)
         P->ivs[i].acc = accs + i;
@@ -867,10 +910,12 @@ int launch_seq(const Planned& P, bool iv_by_value, bool profile, void* out_summa
     Acc* accs = P.ivs.empty() ? nullptr : P.ivs[0].acc;
     hipError_t e;
     int rc;
-    if ((e = launch_prepare(L, accs, iv_by_value ? &P.ivs[0] : nullptr, (uint32_t)P.nseg_total,
-                            s)) != hipSuccess)
+    if ((e = launch_prepare(L, accs, iv_by_value ? &P.ivs[0] : nullptr,
+                            P.n_ranges ? 0u : (uint32_t)P.nseg_total, s)) != hipSuccess)
         return hip_fail(e, "k_prepare");
-    if (P.any_bucket && (e = launch_bucket(L, P.n_heavy, P.max_direct, P.max_cof, s)) != hipSuccess)
+    if (P.any_bucket && (e = launch_bucket(L, P.n_heavy, P.max_direct, P.max_cof, P.p_cof, P.in_doubles,
+                                           P.ranges.empty() ? nullptr : (const uint4*)(P.base + P.o_ranges), P.n_ranges,
+                                           s)) != hipSuccess)
         return hip_fail(e, "k_bucket");
     std::pair<hipEvent_t, hipEvent_t> ev;
     if (profile && (rc = prof_begin(s, &ev)))
@@ -987,6 +1032,10 @@ int enqueue(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vecto
         if (!P.items.empty()) {
             parts.push_back({P.items.data(), sizeof(uint4) * P.items.size()});
             dsts.push_back(base + P.o_items);
+        }
+        if (!P.ranges.empty()) {
+            parts.push_back({P.ranges.data(), sizeof(uint4) * P.ranges.size()});
+            dsts.push_back(base + P.o_ranges);
         }
         if ((rc = stage_upload(parts, dsts, s))) {
             release();
@@ -1169,21 +1218,16 @@ int esq_init(int device, uint64_t max_hi)
         std::vector<double> pref(pr.size() + 1, 0.0);
         for (size_t i = 0; i < pr.size(); i++)
             pref[i + 1] = pref[i] + 1.0 / ((double)pr[i] * (double)pr[i]);
-        // coarse index for the cofactor pass: idx[v] = first prime >= v * 256
-        const uint32_t pidx_n = (uint32_t)((need >> kPidxShift) + 3);
-        std::vector<uint32_t> idx(pidx_n);
-        for (uint32_t v = 0, i = 0; v < pidx_n; v++) {
-            const uint64_t bound = (uint64_t)v << kPidxShift;
-            while (i < pr.size() && pr[i] < bound)
-                i++;
-            idx[v] = i;
-        }
+        // the bitmap of odd primes up to `need`, for the cofactor pass
+        std::vector<uint32_t> bits(need / 64 + 1, 0u);
+        for (uint32_t p : pr)
+            bits[p >> 6] |= 1u << ((p >> 1) & 31u);
         // Barrett reciprocals floor(2^64 / p^2) of the primes the large-prime
-        // pass reduces by (p <= kCofactorPrime), 8-byte aligned after the index
+        // pass reduces by (p <= kCofactorPrime), 8-byte aligned after the bitmap
         const size_t n_main = pr.size();
         const uint32_t n_qinv = (uint32_t)(std::upper_bound(pr.begin(), pr.end(),
                                                             (uint32_t)kCofactorPrime) - pr.begin());
-        pr.insert(pr.end(), idx.begin(), idx.end());
+        pr.insert(pr.end(), bits.begin(), bits.end());
         if (pr.size() & 1)
             pr.push_back(0);
         const size_t qinv_at = pr.size();  // in uint32 units
@@ -1209,7 +1253,6 @@ int esq_init(int device, uint64_t max_hi)
             (void)hipFree(c->d_primes);
         }
         c->d_primes = d;
-        c->pidx_n = pidx_n;
         c->primes.swap(pr);
         c->inv_pref.swap(pref);
         c->plimit = need;
@@ -1400,7 +1443,10 @@ int esq_batch_create(uint32_t count, const uint64_t* lo, const uint64_t* hi, uin
                        hipMemcpyHostToDevice)) != hipSuccess ||
         (!b->P.items.empty() &&
          (e = hipMemcpy(b->base + b->P.o_items, b->P.items.data(),
-                        sizeof(uint4) * b->P.items.size(), hipMemcpyHostToDevice)) != hipSuccess)) {
+                        sizeof(uint4) * b->P.items.size(), hipMemcpyHostToDevice)) != hipSuccess) ||
+        (!b->P.ranges.empty() &&
+         (e = hipMemcpy(b->base + b->P.o_ranges, b->P.ranges.data(),
+                        sizeof(uint4) * b->P.ranges.size(), hipMemcpyHostToDevice)) != hipSuccess)) {
         (void)hipFree(b->base);
         delete b;
         return hip_fail(e, "hipMemcpy(batch descriptors)");

@@ -53,7 +53,7 @@ constexpr int kMaxSegLog2 = 20;
 constexpr uint32_t kFlushSegs = 4096;     // segments per run and per flush of partial totals
 constexpr int kMinSegLog2 = 10;
 constexpr uint32_t kFinalizeSortCap = 16384;  // LDS sort capacity of the finalize pass
-constexpr uint32_t kPidxShift = 8;        // coarse prime index: 256 integers per entry
+constexpr uint32_t kOwnSegs = 256;        // segments per workgroup of k_bucket_own, at most
 constexpr uint64_t kCofactorPrime = 1u << 20; // largest direct/cofactor cut-over considered
 
 // Per-interval accumulators in device scratch.
@@ -80,6 +80,7 @@ struct Interval {
     uint8_t* out_mink;      // per-n bytes (n-index - I0), or null
     uint64_t* out_bits;     // sieve output words, or null
     uint32_t out_shift;     // sieve: I0 - A0
+    double sqrt_lo, sqrt_hi; // square roots of the least and the largest odd number of its regions
     uint32_t n_cof_wide;    // the first n_cof_wide cofactors (widest ranges) take 8 lanes each
 };
 
@@ -108,8 +109,8 @@ struct Launch {
     const Interval* iv;
     const uint4* items;           // (interval, first segment, segments, 0), or null
     const uint32_t* primes;       // odd primes ascending
-    const uint32_t* pidx;         // pidx[v]: index of the first prime >= v << kPidxShift
-    uint32_t pidx_n;              // entries of pidx
+    const uint32_t* pbits;        // bit i: 2 i + 1 is prime, for the odd numbers up to plimit
+    uint32_t plimit;
     const uint64_t* qinv;         // qinv[i] = floor(2^64 / primes[i]^2) for i < n_qinv
     uint32_t n_qinv;              // every prime <= kCofactorPrime has one
     const uint2* medq;            // per medium prime: (q, S mod q)
@@ -141,7 +142,7 @@ hipError_t launch_col_build(uint32_t* tab, hipStream_t s);
 hipError_t launch_prepare(const Launch& L, Acc* accs, const Interval* iv_single,
                           uint32_t nseg_total, hipStream_t s);
 hipError_t launch_bucket(const Launch& L, uint32_t n_heavy, uint32_t max_direct, uint32_t max_cof,
-                         hipStream_t s);
+                         uint32_t p_cof, bool in_doubles, const uint4* ranges, uint32_t n_ranges, hipStream_t s);
 hipError_t launch_verify(const Launch& L, uint32_t grid, uint32_t block, hipStream_t s);
 hipError_t launch_tail(const Launch& L, hipStream_t s);
 hipError_t launch_finalize(const Launch& L, void* out_summaries, void* out_records,

@@ -7,7 +7,9 @@
 //   k_bucket       primes above the medium range: every odd multiple of p^2
 //                  that falls in a segment region goes to that segment's hit
 //                  slots (by first hit up to a cut-over chosen per launch, at
-//                  most 2^20; by cofactor enumeration above it)
+//                  most 2^20; by cofactor enumeration above it); k_bucket_own
+//                  where there are segments enough to give each workgroup its
+//                  own
 //   k_column       k_verify's summary form in the column layout: the default
 //                  for aggregates-only calls
 //   k_verify       persistent workgroups pull runs of consecutive segments;
@@ -117,6 +119,8 @@ __device__ __forceinline__ void g_or(unsigned int* p, unsigned int v)
     __hip_atomic_fetch_or((g_uint*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+__device__ __forceinline__ uint32_t rfl(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
+
 // popcount(x) + acc in one v_bcnt_u32_b32
 __device__ __forceinline__ uint32_t bcnt_acc(uint32_t x, uint32_t acc)
 {
@@ -208,135 +212,305 @@ __device__ __forceinline__ uint64_t isqrt_floor(uint64_t x)
     return r;
 }
 
+// first_hit in doubles, for |B0| < 2^52 and q < 2^41, inv close to 1 / q: the
+// quotient's floor is off by at most one, the remainder's fma is exact, and
+// two corrections finish it.  A tenth of the issue time of the 64-bit integer
+// reduction, whose multiplies run at a quarter of the rate or less.
+__device__ __forceinline__ double first_hit_d(double B0, double q, double inv)
+{
+    const double d = (q - 1.0) * 0.5 - B0;
+    double r = __builtin_fma(-__builtin_floor(d * inv), q, d);
+    r = r < 0.0 ? r + q : r;
+    return r >= q ? r - q : r;
+}
+
+// 1 / q to within a few units in the last place
+__device__ __forceinline__ double recip_d(double q)
+{
+    const double y = __builtin_amdgcn_rcp(q);
+    return __builtin_fma(__builtin_fma(-q, y, 1.0), y, y);
+}
+
 // Segment s of an interval covers region offsets y in [s S, s S + R): a hit
 // belongs to segment floor(y / S) and to each earlier segment still reaching it.
-__device__ __forceinline__ void bucket_emit(const Launch& L, const Interval& iv, uint64_t y)
+// A hit's slot number comes back from a device-scope atomic, microseconds
+// later: the hits y, y + step, ... < E go out kEmit at a time.
+constexpr int kEmit = 4;
+__device__ __forceinline__ void bucket_emit(const Launch& L, uint32_t seg_base, uint32_t nseg, uint64_t y,
+                                            uint64_t step, uint64_t E)
 {
     const uint64_t S = L.S;
-    const uint64_t R = (uint64_t)L.rw * 64;
-    // y div S through the reciprocal: at most one too small (y < 2^56)
-    uint64_t seg = __umul64hi(y, L.s_inv);
-    uint64_t off = y - seg * S;
-    if (off >= S) {
-        seg++;
-        off -= S;
-    }
-    while (off < R) {
-        if (seg < iv.nseg) {
-            const uint32_t gs = iv.seg_base + (uint32_t)seg;
-            const uint32_t pos = atomicAdd(&L.bucket_cnt[gs], 1u);
-            if (pos < L.bucket_cap)
-                L.bucket_slot[(uint64_t)gs * L.bucket_cap + pos] = (uint32_t)off;
+    const uint32_t R = L.rw * 64;
+    while (y < E) {
+        uint64_t seg[kEmit];
+        uint32_t off[kEmit], pos[kEmit];
+        bool again = false;
+#pragma unroll
+        for (int u = 0; u < kEmit; u++) {
+            const uint64_t yu = y + u * step;
+            // y div S through the reciprocal: at most one too small (y < 2^56)
+            seg[u] = __umul64hi(yu, L.s_inv);
+            off[u] = (uint32_t)(yu - seg[u] * S);
+            if (off[u] >= S) {
+                seg[u]++;
+                off[u] -= (uint32_t)S;
+            }
+            const bool in = yu < E;
+            again = again || (in && off[u] + S < R);
+            pos[u] = ~0u;
+            if (in && seg[u] < nseg)
+                pos[u] = atomicAdd(&L.bucket_cnt[seg_base + seg[u]], 1u);
+            else if (!in)
+                seg[u] = 0;
         }
-        if (seg == 0)
-            break;
-        seg--;
-        off += S;
+#pragma unroll
+        for (int u = 0; u < kEmit; u++)
+            if (pos[u] < L.bucket_cap)
+                L.bucket_slot[(seg_base + seg[u]) * L.bucket_cap + pos[u]] = off[u];
+        if (again)  // hits in the overlap with earlier segments
+            for (int u = 0; u < kEmit; u++) {
+                uint64_t g = seg[u];
+                uint64_t o = off[u] + S;
+                while (y + u * step < E && o < R && g > 0) {
+                    g--;
+                    const uint32_t at = atomicAdd(&L.bucket_cnt[seg_base + g], 1u);
+                    if (at < L.bucket_cap)
+                        L.bucket_slot[(seg_base + g) * L.bucket_cap + at] = (uint32_t)o;
+                    o += S;
+                }
+            }
+        y += kEmit * step;
     }
 }
 
-// grid.y = interval.  Work units, in order: kHeavyLanes-wide groups of lanes
-// for each of the first n_heavy bucket primes (many hits: the group strides
-// over them), then one thread per remaining prime of the direct range
-// primes[med_end, b_direct_end), then, for the primes above it, kCofactorLanes
-// lanes for each of the first n_cof_wide odd cofactors j (wide ranges) and one
-// thread for each remaining j.
-constexpr uint32_t kHeavyLanes = 64;
-constexpr uint32_t kCofactorLanes = 8;
-
-__global__ __launch_bounds__(256) void k_bucket(Launch L, uint32_t n_heavy, uint32_t max_direct)
+// The odd cofactor j's odd multiples j p^2 in the regions whose least and
+// largest odd number have the square roots sqrt_lo and sqrt_hi: the p form one
+// range, empty for most j when the regions are short.  Its ends, to within
+// 1e-6 (p < 2^28), and whether an integer no smaller than p_cof lies in it.
+__device__ __forceinline__ bool cofactor_range(uint64_t j, double sqrt_lo, double sqrt_hi, uint32_t p_cof,
+                                               double* lo_d, double* hi_d)
 {
-    const Interval iv = L.iv[blockIdx.y];
-    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t B0 = iv.A0 - (int64_t)L.hlo_words * 64 - (int64_t)L.origin;  // region bit 0
-    const uint64_t S = L.S;
-    const uint64_t E = (uint64_t)(iv.nseg ? iv.nseg - 1 : 0) * S + (uint64_t)L.rw * 64;
-    if (iv.nseg == 0)
-        return;
-    const uint64_t heavy_units = (uint64_t)n_heavy * kHeavyLanes;
-    if (t < heavy_units) {
-        const uint64_t pi = L.med_end + t / kHeavyLanes;
-        const uint32_t g = (uint32_t)(t % kHeavyLanes);
-        if (pi >= iv.b_direct_end)
-            return;
-        const uint64_t p = L.primes[pi];
-        const uint64_t q = p * p;
-        const uint64_t f = pi < L.n_qinv ? first_hit_b(B0, q, L.qinv[pi]) : first_hit(B0, q);
-        for (uint64_t y = f + g * q; y < E; y += kHeavyLanes * q)
-            bucket_emit(L, iv, y);
-        return;
-    }
-    const uint64_t td = t - heavy_units;
-    if (td < max_direct) {
-        const uint64_t pi = L.med_end + n_heavy + td;
-        if (pi >= iv.b_direct_end)
-            return;
-        const uint64_t p = L.primes[pi];
-        const uint64_t q = p * p;
-        const uint64_t f = pi < L.n_qinv ? first_hit_b(B0, q, L.qinv[pi]) : first_hit(B0, q);
-        for (uint64_t y = f; y < E; y += q)
-            bucket_emit(L, iv, y);
-        return;
-    }
-    // odd multiples j p^2 of the primes above the direct range, one thread
-    // per odd cofactor j: the p with j p^2 in [m_lo, m_hi] form one range,
-    // empty for most j when the interval is short
-    const uint64_t tc = td - max_direct;
-    const uint64_t wide_threads = (uint64_t)iv.n_cof_wide * kCofactorLanes;
-    uint64_t c;
-    uint32_t g = 0, lanes = 1;
-    if (tc < wide_threads) {
-        c = tc / kCofactorLanes;
-        g = (uint32_t)(tc % kCofactorLanes);
-        lanes = kCofactorLanes;
-    } else {
-        c = iv.n_cof_wide + (tc - wide_threads);
-    }
-    if (c >= iv.n_cof || iv.b_direct_end >= iv.pmax_end)
-        return;
-    const uint64_t j = 2 * c + 1;
+    const double jd = (double)j;
+    double y = __builtin_amdgcn_rsq(jd);
+    y = __builtin_fma(__builtin_fma(-jd * y, y, 1.0), 0.5 * y, y);
+    *lo_d = sqrt_lo * y - 1e-4;
+    *hi_d = __builtin_floor(sqrt_hi * y + 1e-4);
+    return *hi_d >= *lo_d && *hi_d >= (double)p_cof;
+}
+
+// hit(y) for the region offset y of each of j's multiples of a prime p >= p_cof
+// in that range, by lanes g, g + lanes, ...; the regions' bit 0 is odd index B0
+// and they hold E bits.  The range's ends come from the estimates by exact
+// corrections; a p is looked up in the bitmap of odd primes (one load, where a
+// search in the prime table is a chain of them).
+template <typename Hit>
+__device__ __forceinline__ void cofactor_hits(const Launch& L, uint64_t j, double lo_d, double hi_d, int64_t B0,
+                                              uint64_t E, uint32_t p_cof, uint32_t g, uint32_t lanes, Hit hit)
+{
     const uint64_t m_lo = B0 > 0 ? 2 * (uint64_t)B0 + 1 : 1;
     const uint64_t m_hi = 2 * (uint64_t)(B0 + (int64_t)E - 1) + 1;
-    // least pa with j pa^2 >= m_lo and largest pb with j pb^2 <= m_hi: a
-    // double estimate (within one of the answer), then exact corrections
-    uint64_t pa = (uint64_t)sqrt((double)m_lo / (double)j);
+    uint64_t pa = lo_d > 0.0 ? (uint64_t)lo_d : 0;
     while (pa > 0 && j * pa * pa >= m_lo)
         pa--;
     while (j * pa * pa < m_lo)
         pa++;
-    uint64_t pb = (uint64_t)sqrt((double)m_hi / (double)j) + 1;
+    uint64_t pb = (uint64_t)hi_d + 1;
     while (j * pb * pb > m_hi)
         pb--;
-    if (pa > pb || pb < (uint64_t)L.primes[iv.b_direct_end])
-        return;
-    // first prime >= pa among primes[b_direct_end, pmax_end): the coarse
-    // index narrows the search to one 256-wide stretch of integers
-    const uint64_t v = min(pa >> kPidxShift, (uint64_t)L.pidx_n - 2);
-    uint32_t lo = L.pidx[v], hi = L.pidx[v + 1];
-    while (lo < hi) {
-        const uint32_t mid = lo + (hi - lo) / 2;
-        if ((uint64_t)L.primes[mid] < pa)
-            lo = mid + 1;
-        else
-            hi = mid;
-    }
-    lo = max(lo, iv.b_direct_end);
-    for (uint32_t i = lo + g; i < iv.pmax_end; i += lanes) {
-        const uint64_t p = L.primes[i];
-        if (p > pb)
-            break;
-        bucket_emit(L, iv, (j * p * p - 1) / 2 - (uint64_t)B0);
-    }
+    pb = min(pb, (uint64_t)L.plimit);
+    for (uint64_t p = (max(pa, (uint64_t)p_cof) | 1) + 2 * g; p <= pb; p += 2 * lanes)
+        if (L.pbits[p >> 6] >> ((p >> 1) & 31u) & 1u)
+            hit((j * p * p - 1) / 2 - (uint64_t)B0);
 }
 
-hipError_t launch_bucket(const Launch& L, uint32_t n_heavy, uint32_t max_direct, uint32_t max_cof,
-                         hipStream_t s)
+typedef const __attribute__((address_space(4))) Interval CInterval;
+
+// Few segments: grid.y = interval.  Work units, in order: kHeavyLanes-wide
+// groups of lanes for each of the first n_heavy bucket primes (many hits: the
+// group strides over them), then one thread per remaining prime of the direct
+// range primes[med_end, b_direct_end), then, for the primes above it
+// (p_cof and up), kCofactorLanes lanes for each of the first n_cof_wide odd
+// cofactors j (wide ranges) and one thread for each remaining j.
+constexpr uint32_t kHeavyLanes = 64;
+constexpr uint32_t kCofactorLanes = 8;
+
+__global__ __launch_bounds__(256) void k_bucket(Launch L, uint32_t n_heavy, uint32_t max_direct, uint32_t p_cof,
+                                                int in_doubles)
 {
+    CInterval* iv = (CInterval*)(uintptr_t)(L.iv + blockIdx.y);
+    const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const uint64_t heavy_units = (uint64_t)n_heavy * kHeavyLanes;
+    if (iv->nseg == 0)
+        return;
+    const int64_t B0 = iv->A0 - (int64_t)L.hlo_words * 64 - (int64_t)L.origin;  // region bit 0
+    const uint64_t E = (uint64_t)(iv->nseg - 1) * L.S + (uint64_t)L.rw * 64;
+    if (t < heavy_units + max_direct) {
+        const bool heavy = t < heavy_units;
+        const uint64_t pi = L.med_end + (heavy ? t / kHeavyLanes : n_heavy + (t - heavy_units));
+        if (pi >= iv->b_direct_end)
+            return;
+        const uint64_t p = L.primes[pi];
+        const uint64_t q = p * p;
+        uint64_t f;
+        if (in_doubles)
+            f = (uint64_t)first_hit_d((double)B0, (double)q, recip_d((double)q));
+        else
+            f = pi < L.n_qinv ? first_hit_b(B0, q, L.qinv[pi]) : first_hit(B0, q);
+        const uint64_t g = heavy ? t % kHeavyLanes : 0, stride = heavy ? kHeavyLanes : 1;
+        bucket_emit(L, iv->seg_base, iv->nseg, f + g * q, stride * q, E);
+        return;
+    }
+    const uint64_t tc = t - heavy_units - max_direct;
+    const uint64_t wide_threads = (uint64_t)iv->n_cof_wide * kCofactorLanes;
+    const bool wide = tc < wide_threads;
+    const uint64_t c = wide ? tc / kCofactorLanes : iv->n_cof_wide + (tc - wide_threads);
+    if (c >= iv->n_cof)
+        return;
+    double lo_d, hi_d;
+    if (cofactor_range(2 * c + 1, iv->sqrt_lo, iv->sqrt_hi, p_cof, &lo_d, &hi_d))
+        cofactor_hits(L, 2 * c + 1, lo_d, hi_d, B0, E, p_cof, wide ? (uint32_t)(tc % kCofactorLanes) : 0u,
+                      wide ? kCofactorLanes : 1u,
+                      [&](uint64_t y) { bucket_emit(L, iv->seg_base, iv->nseg, y, E, y + 1); });
+}
+
+// Many segments: a workgroup owns up to kOwnSegs consecutive segments of one
+// interval, takes every bucket prime and every cofactor over them, and counts
+// their hits in LDS, so no counter is shared between workgroups (nor cleared
+// beforehand).  Counters in memory bound the other form here: the dies' atomic
+// operations on them pass the L2 caches, about ten in a nanosecond.  What is
+// left to bound it is finding out that a prime or cofactor has no hit in the
+// range, about a dozen double-precision operations each, 3e4 of them per
+// workgroup near 2^50.  1024 intervals of 2^16 .. 2^28 odd n: 156 us with
+// 64-bit integer reductions, exact square roots for all and counters in memory,
+// 110 with the arithmetic in doubles, 57 here; 2^33 odd n: 20 and 16 us.
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void k_bucket_own(Launch L, const uint4* ranges, uint32_t p_cof, int in_doubles)
+{
+    __shared__ uint32_t s_cnt[kOwnSegs];
+    // The cofactors with an integer in their range and the primes with a hit,
+    // about one in a hundred and one in twenty: listed, then a lane each for
+    // the rest of their work, which every wave would go through for the sake
+    // of a lane or two otherwise.
+    constexpr uint32_t kListed = 2048;
+    __shared__ uint32_t s_cof[kListed], s_prime[kListed], s_hit[kListed];
+    __shared__ uint32_t s_n_cof, s_n_prime;
+    uint32_t ivi = 0, s0, n;
+    if (ranges) {
+        const uint4 r = ranges[blockIdx.x];
+        ivi = rfl(r.x);
+        s0 = rfl(r.y);
+        n = rfl(r.z);
+    } else {
+        const uint64_t ns = L.iv[0].nseg;
+        s0 = (uint32_t)(blockIdx.x * ns / gridDim.x);
+        n = (uint32_t)((blockIdx.x + 1) * ns / gridDim.x) - s0;
+    }
+    CInterval* iv = (CInterval*)(uintptr_t)(L.iv + ivi);
+    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x)
+        s_cnt[i] = 0;
+    if (threadIdx.x == 0)
+        s_n_cof = s_n_prime = 0;
+    __syncthreads();
+    const uint32_t S = L.S, R = L.rw * 64, cap = L.bucket_cap;
+    const uint32_t gs = iv->seg_base + s0;
+    // the range's regions: E bits from odd index B0 (E < 2^32)
+    const int64_t B0 = iv->A0 - (int64_t)L.hlo_words * 64 - (int64_t)L.origin + (int64_t)s0 * (int64_t)S;
+    const uint64_t E = (uint64_t)(n - 1) * S + R;
+    uint32_t* slots = L.bucket_slot + (uint64_t)gs * cap;
+    auto emit = [&](uint64_t y) {  // y < E: to its segment and each earlier one that still reaches it
+        uint32_t seg = (uint32_t)__umul64hi(y, L.s_inv);
+        uint32_t off = (uint32_t)y - seg * S;
+        if (off >= S) {
+            seg++;
+            off -= S;
+        }
+        for (; off < R; off += S) {
+            if (seg < n) {
+                const uint32_t pos = atomicAdd(&s_cnt[seg], 1u);
+                if (pos < cap)
+                    slots[(uint64_t)seg * cap + pos] = off;
+            }
+            if (seg == 0)
+                break;
+            seg--;
+        }
+    };
+    const uint32_t n_direct = iv->b_direct_end - L.med_end, n_cof = iv->n_cof;
+    const double Ed = (double)E, B0d = (double)B0;
+    const double sqrt_lo = sqrt(B0 > 0 ? 2.0 * B0d + 1.0 : 1.0), sqrt_hi = sqrt(2.0 * (B0d + Ed) - 1.0);
+    auto cofactor = [&](uint32_t c) {
+        double lo_d, hi_d;
+        if (cofactor_range(2 * (uint64_t)c + 1, sqrt_lo, sqrt_hi, p_cof, &lo_d, &hi_d))
+            cofactor_hits(L, 2 * (uint64_t)c + 1, lo_d, hi_d, B0, E, p_cof, 0u, 1u, emit);
+    };
+    for (uint32_t c = threadIdx.x; c < n_cof; c += blockDim.x) {
+        double lo_d, hi_d;
+        if (cofactor_range(2 * (uint64_t)c + 1, sqrt_lo, sqrt_hi, p_cof, &lo_d, &hi_d)) {
+            const uint32_t at = atomicAdd(&s_n_cof, 1u);
+            if (at < kListed)
+                s_cof[at] = c;
+            else
+                cofactor(c);
+        }
+    }
+    constexpr int kAhead = 4;  // primes per thread in flight
+    for (uint32_t t0 = threadIdx.x; t0 < n_direct; t0 += kAhead * blockDim.x) {
+        uint32_t pr[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; u++)
+            pr[u] = L.primes[min(L.med_end + t0 + u * blockDim.x, L.nprimes - 1)];
+#pragma unroll
+        for (int u = 0; u < kAhead; u++) {
+            const uint32_t t = t0 + u * blockDim.x;
+            const uint64_t q = (uint64_t)pr[u] * pr[u];
+            uint64_t f = E;
+            if (t < n_direct) {
+                if (in_doubles) {
+                    const double fd = first_hit_d(B0d, (double)q, recip_d((double)q));
+                    if (fd < Ed)
+                        f = (uint64_t)fd;
+                } else {
+                    const uint32_t pi = L.med_end + t;
+                    f = pi < L.n_qinv ? first_hit_b(B0, q, L.qinv[pi]) : first_hit(B0, q);
+                }
+            }
+            if (f < E) {
+                const uint32_t at = atomicAdd(&s_n_prime, 1u);
+                if (at < kListed) {
+                    s_prime[at] = pr[u];
+                    s_hit[at] = (uint32_t)f;
+                } else {
+                    for (; f < E; f += q)
+                        emit(f);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    // the two lists from opposite ends of the workgroup
+    const uint32_t n_listed = min(s_n_prime, kListed), c_listed = min(s_n_cof, kListed);
+    for (uint32_t i = threadIdx.x; i < n_listed; i += blockDim.x)
+        for (uint64_t f = s_hit[i], q = (uint64_t)s_prime[i] * s_prime[i]; f < E; f += q)
+            emit(f);
+    for (uint32_t i = blockDim.x - 1 - threadIdx.x; i < c_listed; i += blockDim.x)
+        cofactor(s_cof[i]);
+    __syncthreads();
+    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x)
+        L.bucket_cnt[gs + i] = s_cnt[i];
+}
+
+hipError_t launch_bucket(const Launch& L, uint32_t n_heavy, uint32_t max_direct, uint32_t max_cof, uint32_t p_cof,
+                         bool in_doubles, const uint4* ranges, uint32_t n_ranges, hipStream_t s)
+{
+    if (n_ranges) {
+        hipLaunchKernelGGL(k_bucket_own, dim3(n_ranges), dim3(1024), 0, s, L, ranges, p_cof, in_doubles ? 1 : 0);
+        return hipGetLastError();
+    }
     const uint64_t threads = (uint64_t)n_heavy * kHeavyLanes + max_direct + (uint64_t)max_cof;
     if (threads == 0 || L.n_iv == 0)
         return hipSuccess;
     const uint32_t bx = (uint32_t)((threads + 255) / 256);
-    hipLaunchKernelGGL(k_bucket, dim3(bx, L.n_iv), dim3(256), 0, s, L, n_heavy, max_direct);
+    hipLaunchKernelGGL(k_bucket, dim3(bx, L.n_iv), dim3(256), 0, s, L, n_heavy, max_direct, p_cof,
+                       in_doubles ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -512,8 +686,6 @@ __device__ __forceinline__ void stage_store_run(u32x4* st, g_u8* out, const uint
 // phase-clock sums), then the medium primes' (q, S mod q), their current
 // first-hit offsets, the lane-task table when it fits, and in per-n mode
 // (when it fits) one store-staging area per wave, 16-byte aligned.
-__device__ __forceinline__ uint32_t rfl(uint32_t x) { return __builtin_amdgcn_readfirstlane(x); }
-
 // MODE 0: verify, aggregates only; MODE 1: verify + per-n bytes;
 // MODE 2: Algorithm 1 alone, bitmap to HBM.  PH: the phase-clock instance
 // (measurement only).
