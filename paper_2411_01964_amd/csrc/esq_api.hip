@@ -928,7 +928,7 @@ int launch_seq(const Planned& P, bool iv_by_value, bool profile, void* out_summa
     if (P.mode != 2) {
         if ((e = launch_tail(L, s)) != hipSuccess)
             return hip_fail(e, "k_tail");
-        if ((e = launch_finalize(L, out_summaries, out_records, out_exceptions, exc_cap, s)) !=
+        if ((e = launch_finalize(L, accs, out_summaries, out_records, out_exceptions, exc_cap, s)) !=
             hipSuccess)
             return hip_fail(e, "k_finalize");
     }

@@ -61,7 +61,6 @@ struct Acc {
     unsigned long long cnt[16];        // cnt[k]: #n still unresolved after step k (k <= k_lds)
     unsigned long long first[65];      // first[k]: least n-index with depth >= k
     unsigned long long deep_hist[65];  // tail pass: [0] no representation, [k] least k
-    unsigned long long tail_count;     // #n of this interval sent to the tail pass
     unsigned int status;               // ESQ_STATUS_* bits
     unsigned int pad;
 };
@@ -145,7 +144,7 @@ hipError_t launch_bucket(const Launch& L, uint32_t n_heavy, uint32_t max_direct,
                          uint32_t p_cof, bool in_doubles, const uint4* ranges, uint32_t n_ranges, hipStream_t s);
 hipError_t launch_verify(const Launch& L, uint32_t grid, uint32_t block, hipStream_t s);
 hipError_t launch_tail(const Launch& L, hipStream_t s);
-hipError_t launch_finalize(const Launch& L, void* out_summaries, void* out_records,
+hipError_t launch_finalize(const Launch& L, const Acc* accs, void* out_summaries, void* out_records,
                            uint64_t* out_exceptions, uint64_t exc_cap, hipStream_t s);
 hipError_t configure_kernels();
 int verify_occupancy(int mode, uint32_t block, size_t lds_bytes);

@@ -145,7 +145,6 @@ __global__ void k_prepare(Launch L, Acc* accs, Interval iv0, int write_iv0, uint
         a->first[k] = kNone;
         a->deep_hist[k] = 0;
         if (k == 0) {
-            a->tail_count = 0;
             a->status = 0;
             a->pad = 0;
         }
@@ -1333,7 +1332,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
                     // one reservation of popcount(U) list entries per word
                     const uint64_t j0 = j0_of();
                     const unsigned long long c = (unsigned long long)__popcll(U);
-                    g_add(&IV.acc->tail_count, c);
                     unsigned long long idx = atomicAdd(L.tail_count, c);
                     for (uint64_t x = U; x; idx++) {
                         const int bit = __ffsll((unsigned long long)x) - 1;
@@ -1874,7 +1872,6 @@ __global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(8))) 
                     // still unresolved: to the tail pass or the exceptions, as in k_verify
                     if (__builtin_expect(U != 0, 0) && (klds < lp->kmax_eff || lp->exc_list)) {
                         const unsigned long long cu = (unsigned long long)__popc(U);
-                        g_add(&ivp->acc->tail_count, cu);
                         unsigned long long idx = atomicAdd(lp->tail_count, cu);
                         for (uint32_t x = U; x; x &= x - 1, idx++) {
                             if (idx < lp->tail_cap) {
@@ -1969,55 +1966,52 @@ int verify_occupancy(int mode, uint32_t block, size_t lds_bytes)
 
 // --------------------------------------------------------------- tail
 
-// Exact search, by trial division over the resident prime squares, for the
-// n whose first k_lds candidates were all marked (Algorithm 2 continued).
+// Exact search, by trial division over the resident prime squares, for an n
+// (odd index j) whose first k_lds candidates were all marked (Algorithm 2
+// continued), by the whole workgroup: its least k, 0 if none.
+__device__ __forceinline__ uint32_t tail_search(const Launch& L, uint64_t j, int* s_hit)
+{
+    const uint64_t n = 2 * j + 1;
+    volatile int* hitp = s_hit;
+    for (uint32_t k = L.k_lds + 1; k <= 63 && k <= L.kmax_eff; k++) {
+        const uint64_t pk = 1ull << k;
+        if (pk >= n)
+            break;
+        const uint64_t m = n - pk;
+        if (threadIdx.x == 0)
+            *hitp = 0;
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < L.nprimes; i += blockDim.x) {
+            const uint64_t pr = L.primes[i];
+            const uint64_t q = pr * pr;
+            if (q > m || *hitp)
+                break;
+            if (m % q == 0) {
+                *hitp = 1;
+                break;
+            }
+        }
+        __syncthreads();
+        const int hit = *hitp;
+        __syncthreads();
+        if (!hit)
+            return k;
+    }
+    return 0;
+}
+
+// The tail pass as a kernel of its own, where many n are expected to need it
+// (see tail_in_finalize).
 __global__ __launch_bounds__(256) void k_tail(Launch L)
 {
     __shared__ int s_hit;
     const unsigned long long total = *L.tail_count;
     const uint64_t count = total < L.tail_cap ? total : L.tail_cap;
-    volatile int* hitp = &s_hit;
     for (uint64_t idx = blockIdx.x; idx < count; idx += gridDim.x) {
         const uint64_t j = L.tail_n[idx];
-        if (L.k_lds >= L.kmax_eff) {
-            // listed exceptions: no k is left to try, and the counts, first-n
-            // slots and per-n bytes are complete already
-            if (threadIdx.x == 0)
-                L.tail_d[idx] = 0;
-            continue;
-        }
-        const Interval IV = L.iv[L.tail_iv[idx]];
-        const uint64_t n = 2 * j + 1;
-        uint32_t d = 0;
-        for (uint32_t k = L.k_lds + 1; k <= 63; k++) {
-            if (k > L.kmax_eff)
-                break;
-            const uint64_t pk = 1ull << k;
-            if (pk >= n)
-                break;
-            const uint64_t m = n - pk;
-            if (threadIdx.x == 0)
-                *hitp = 0;
-            __syncthreads();
-            for (uint32_t i = threadIdx.x; i < L.nprimes; i += blockDim.x) {
-                const uint64_t pr = L.primes[i];
-                const uint64_t q = pr * pr;
-                if (q > m || *hitp)
-                    break;
-                if (m % q == 0) {
-                    *hitp = 1;
-                    break;
-                }
-            }
-            __syncthreads();
-            const int hit = *hitp;
-            __syncthreads();
-            if (!hit) {
-                d = k;
-                break;
-            }
-        }
+        const uint32_t d = tail_search(L, j, &s_hit);
         if (threadIdx.x == 0) {
+            const Interval IV = L.iv[L.tail_iv[idx]];
             L.tail_d[idx] = (uint8_t)d;
             g_add(&IV.acc->deep_hist[d], 1ull);
             const uint32_t top = d ? d : 64u;
@@ -2029,8 +2023,16 @@ __global__ __launch_bounds__(256) void k_tail(Launch L)
     }
 }
 
+// Whether k_finalize takes the tail pass along.  With the search limit at the
+// in-LDS depth there is none (what is listed are exceptions); at 12 in-LDS
+// steps and more, an n is left with probability 9e-16, so the launch of an
+// empty k_tail (4 us, a fifth of a short call's kernels) is saved.
+static bool tail_in_finalize(const Launch& L) { return L.k_lds >= L.kmax_eff || L.k_lds >= 12; }
+
 hipError_t launch_tail(const Launch& L, hipStream_t s)
 {
+    if (tail_in_finalize(L))
+        return hipSuccess;
     hipLaunchKernelGGL(k_tail, dim3(512), dim3(256), 0, s, L);
     return hipGetLastError();
 }
@@ -2052,41 +2054,67 @@ __device__ unsigned long long block_sum(unsigned long long v, unsigned long long
     return r;
 }
 
-// One workgroup per interval.
-__global__ __launch_bounds__(1024) void k_finalize(Launch L, void* out_summaries, void* out_records,
-                                                   uint64_t* out_exceptions, uint64_t exc_cap)
+// One workgroup per interval; the aggregates by its first wave, a level per
+// lane (one thread taking the 65 levels in turn took 4 of the kernel's 6 us).
+__global__ __launch_bounds__(1024) void k_finalize(Launch L, const Acc* accs, void* out_summaries, void* out_records,
+                                                   uint64_t* out_exceptions, uint64_t exc_cap, int tail)
 {
     extern __shared__ unsigned long long s_sort[];
     __shared__ unsigned long long s_acc;
     __shared__ unsigned int s_fill;
-    __shared__ unsigned long long s_first[65];
+    __shared__ int s_hit;
+    __shared__ unsigned long long s_first[66], s_h[65], s_cnt[16];
     const uint32_t ivi = blockIdx.x;
-    const Interval IV = L.iv[ivi];
-    const Acc* A = IV.acc;
+    CInterval* IV = (CInterval*)(uintptr_t)(L.iv + ivi);
+    const Acc* A = accs + ivi;
     const uint32_t tid = threadIdx.x, T = blockDim.x;
     const unsigned long long tail_total = *L.tail_count;
     const uint64_t nlist = tail_total < L.tail_cap ? tail_total : L.tail_cap;
-    const uint64_t n_odd = IV.I1 - IV.I0;
+    const uint64_t I0 = IV->I0, n_odd = IV->I1 - I0;
+    const uint32_t status = A->status;
     // with the search limit at the in-LDS depth there is no tail pass: the n
     // still unresolved after step k_lds are the exceptions, and they are
     // deeper than every level, so first[k] for k > k_lds + 1 is first[k_lds + 1]
     const bool no_tail = L.k_lds >= L.kmax_eff;
-    const uint64_t n_exc = no_tail ? A->cnt[L.k_lds] : A->deep_hist[0];
-    const uint64_t want = n_exc < exc_cap ? n_exc : exc_cap;
-    for (uint32_t i = tid; i < 65; i += T)
+    for (uint32_t i = tid; i < 65; i += T) {
         s_first[i] = (no_tail && i > L.k_lds + 1) ? A->first[L.k_lds + 1] : A->first[i];
+        s_h[i] = no_tail ? 0ull : A->deep_hist[i];
+        if (i < 16)
+            s_cnt[i] = A->cnt[i];
+    }
+    __syncthreads();
+    if (tail && !no_tail)
+        for (uint64_t idx = 0; idx < nlist; idx++) {
+            if (L.tail_iv[idx] != ivi)
+                continue;
+            const uint64_t j = L.tail_n[idx];
+            const uint32_t d = tail_search(L, j, &s_hit);
+            if (tid == 0) {
+                L.tail_d[idx] = (uint8_t)d;
+                s_h[d]++;
+                for (uint32_t kk = L.k_lds + 2; kk <= (d ? d : 64u); kk++)
+                    s_first[kk] = min(s_first[kk], (unsigned long long)j);
+                if (IV->out_mink)
+                    ((g_u8*)IV->out_mink)[j - I0] = (uint8_t)d;
+            }
+            __threadfence_block();
+            __syncthreads();
+        }
+    const uint64_t n_exc = no_tail ? s_cnt[L.k_lds] : s_h[0];
+    const uint64_t want = n_exc < exc_cap ? n_exc : exc_cap;
+    auto listed = [&](uint64_t i) { return L.tail_iv[i] == ivi && (no_tail || L.tail_d[i] == 0); };
 
     if (out_exceptions && want > 0) {
         // the want-th smallest exception of this interval (binary search on
         // its odd index), then an LDS sort of those up to it
         uint64_t thr = kNone;
         if (want < n_exc) {
-            uint64_t lo = 0, hi = 1ull << 56;
+            uint64_t lo = I0, hi = I0 + n_odd;
             while (lo < hi) {
                 const uint64_t mid = lo + (hi - lo) / 2;
                 unsigned long long c = 0;
                 for (uint64_t i = tid; i < nlist; i += T)
-                    c += (L.tail_iv[i] == ivi && L.tail_d[i] == 0 && L.tail_n[i] <= mid) ? 1ull : 0ull;
+                    c += (listed(i) && L.tail_n[i] <= mid) ? 1ull : 0ull;
                 c = block_sum(c, &s_acc);
                 if (c >= want)
                     hi = mid;
@@ -2098,110 +2126,123 @@ __global__ __launch_bounds__(1024) void k_finalize(Launch L, void* out_summaries
         if (tid == 0)
             s_fill = 0;
         __syncthreads();
-        for (uint64_t i = tid; i < nlist; i += T)
-            if (L.tail_iv[i] == ivi && L.tail_d[i] == 0 && L.tail_n[i] <= thr) {
-                const unsigned int slot = atomicAdd(&s_fill, 1u);
-                if (slot < kFinalizeSortCap)
-                    s_sort[slot] = L.tail_n[i];
+        for (uint64_t i0 = tid; i0 < nlist; i0 += 4 * T) {
+            unsigned long long x[4];
+            bool take[4];
+#pragma unroll
+            for (int u = 0; u < 4; u++) {
+                const uint64_t i = min(i0 + u * T, nlist - 1);
+                x[u] = L.tail_n[i];
+                take[u] = listed(i) && i0 + u * T < nlist;
             }
+#pragma unroll
+            for (int u = 0; u < 4; u++)
+                if (take[u] && x[u] <= thr) {
+                    const unsigned int slot = atomicAdd(&s_fill, 1u);
+                    if (slot < kFinalizeSortCap)
+                        s_sort[slot] = x[u];
+                }
+        }
         __syncthreads();
         const uint32_t got = min(s_fill, kFinalizeSortCap);
-        uint32_t n2 = 1;
+        uint32_t n2 = T;  // a power of two
         while (n2 < got)
             n2 <<= 1;
         for (uint32_t i = got + tid; i < n2; i += T)
             s_sort[i] = kNone;
         __syncthreads();
+        // bitonic sort; each wave holds a contiguous stretch, so only the steps
+        // whose partners lie further apart than that need the workgroup's
+        // barrier (10 of 78 for 4096 entries; with one at each, and half the
+        // lanes idle, the kernel took 62 us for 2400 exceptions, now 31)
+        const uint32_t stretch = n2 / (T >> 6), w0 = (tid >> 6) * stretch;
+        bool wide = false;  // the last step crossed stretches
         for (uint32_t k = 2; k <= n2; k <<= 1)
             for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-                for (uint32_t i = tid; i < n2; i += T) {
-                    const uint32_t ixj = i ^ j;
-                    if (ixj > i) {
-                        const unsigned long long a = s_sort[i], b = s_sort[ixj];
-                        const bool up = (i & k) == 0;
-                        if ((a > b) == up) {
-                            s_sort[i] = b;
-                            s_sort[ixj] = a;
-                        }
+                if (j >= stretch || wide)
+                    __syncthreads();
+                wide = j >= stretch;
+                // a lane per pair (i, i + j), two pairs in flight
+                const uint32_t t1 = (w0 + stretch) / 2;
+                for (uint32_t t = w0 / 2 + (tid & 63u); t < t1; t += 128) {
+                    uint32_t i[2];
+                    unsigned long long x[2], y[2];
+#pragma unroll
+                    for (int u = 0; u < 2; u++) {
+                        const uint32_t tu = t + 64 * u < t1 ? t + 64 * u : t;
+                        i[u] = 2 * tu - (tu & (j - 1));
+                        x[u] = s_sort[i[u]];
+                        y[u] = s_sort[i[u] + j];
                     }
+#pragma unroll
+                    for (int u = 0; u < 2; u++)
+                        if ((u == 0 || t + 64 < t1) && (x[u] > y[u]) == ((i[u] & k) == 0)) {
+                            s_sort[i[u]] = y[u];
+                            s_sort[i[u] + j] = x[u];
+                        }
                 }
-                __syncthreads();
+                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+                __builtin_amdgcn_wave_barrier();
             }
+        __syncthreads();
         for (uint32_t i = tid; i < want && i < got; i += T)
             out_exceptions[i] = 2 * s_sort[i] + 1;
     }
-    __syncthreads();
-
-    __shared__ unsigned long long h[65];
-    __shared__ unsigned long long s_cnt[16];
-    for (uint32_t i = tid; i < 65; i += T)
-        h[i] = no_tail ? (i == 0 ? n_exc : 0ull) : A->deep_hist[i];
-    for (uint32_t i = tid; i < 16; i += T)
-        s_cnt[i] = A->cnt[i];
-    __syncthreads();
-    if (tid != 0)
+    if (tid >= 64)
         return;
-    esq_summary* out = reinterpret_cast<esq_summary*>(out_summaries) + ivi;
-    unsigned long long prev = n_odd;
-    for (uint32_t k = 1; k <= L.k_lds; k++) {
-        const unsigned long long c = s_cnt[k];
-        h[k] = prev - c;   // the tail pass only fills depths above k_lds
-        prev = c;
-    }
-    unsigned long long ksum = 0;
-    uint32_t kseen = 0;
-    for (uint32_t k = 1; k < 65; k++) {
-        ksum += (unsigned long long)k * h[k];
-        if (h[k])
-            kseen = k;
-    }
+    // lane l: level k = l + 1.  The LDS steps' counts give the levels up to
+    // k_lds, the tail pass the deeper ones.
+    const uint32_t k = tid + 1;
+    unsigned long long h;
+    if (k <= L.k_lds)
+        h = (k == 1 ? n_odd : s_cnt[k - 1]) - s_cnt[k];
+    else
+        h = s_h[k];
+    unsigned long long ksum = (unsigned long long)k * h;
+    for (int o = 32; o > 0; o >>= 1)
+        ksum += __shfl_xor(ksum, o);
+    const uint64_t seen = __ballot(h != 0);
     // record-setters: first[k] = least n-index with depth >= k; each distinct
     // value is a record, labelled with the deepest level sharing it
-    esq_record* rec = out_records ? reinterpret_cast<esq_record*>(out_records) + (uint64_t)ivi * ESQ_RECORDS_CAP
-                                  : nullptr;
-    uint32_t nrec = 0;
-    if (n_odd) {
-        uint32_t k = 1;
-        while (k <= 64) {
-            const unsigned long long v = (k == 1) ? IV.I0 : s_first[k];
-            if (v == kNone)
-                break;
-            uint32_t kk = k;
-            while (kk < 64 && s_first[kk + 1] == v)
-                kk++;
-            if (rec && nrec < ESQ_RECORDS_CAP) {
-                const uint64_t n = 2 * v + 1;
-                rec[nrec].n = n;
-                rec[nrec].k = kk == 64 ? 0u : kk;
-                // an exception found by the search limit, with a larger k
-                // still positive, vs one for which every k with 2^k < n failed
-                rec[nrec].flags = (kk == 64 && L.kmax_eff < 63 && (1ull << (L.kmax_eff + 1)) < n)
-                                      ? (uint32_t)ESQ_RECORD_KMAX_LIMIT : 0u;
-            }
-            nrec++;
-            k = kk + 1;
-        }
+    const unsigned long long v = k == 1 ? I0 : s_first[k];
+    const bool last = k == 64 || s_first[k + 1] != v;
+    const bool is_rec = n_odd && v != kNone && last;
+    const uint64_t recs = __ballot(is_rec);
+    const uint32_t nrec = (uint32_t)__popcll(recs);
+    if (out_records && is_rec) {
+        esq_record* rec = reinterpret_cast<esq_record*>(out_records) + (uint64_t)ivi * ESQ_RECORDS_CAP +
+                          __popcll(recs & ((1ull << tid) - 1));
+        const uint64_t n = 2 * v + 1;
+        rec->n = n;
+        rec->k = k == 64 ? 0u : k;
+        // an exception found by the search limit, with a larger k still
+        // positive, vs one for which every k with 2^k < n failed
+        rec->flags = (k == 64 && L.kmax_eff < 63 && (1ull << (L.kmax_eff + 1)) < n) ? (uint32_t)ESQ_RECORD_KMAX_LIMIT
+                                                                                   : 0u;
     }
-    out->n0 = n_odd ? 2 * IV.I0 + 1 : 0;
-    out->n_odd = n_odd;
-    for (int k = 0; k < 65; k++)
-        out->hist[k] = h[k];
-    out->ksum = ksum;
-    out->kmax_seen = kseen;
-    out->n_records = nrec < ESQ_RECORDS_CAP ? nrec : ESQ_RECORDS_CAP;
-    out->n_exceptions = h[0];
-    out->status = A->status;
-    out->reserved = 0;
+    esq_summary* out = reinterpret_cast<esq_summary*>(out_summaries) + ivi;
+    out->hist[k] = h;
+    if (tid == 0) {
+        out->n0 = n_odd ? 2 * I0 + 1 : 0;
+        out->n_odd = n_odd;
+        out->hist[0] = n_exc;
+        out->ksum = ksum;
+        out->kmax_seen = seen ? 64u - (uint32_t)__clzll((long long)seen) : 0u;
+        out->n_records = nrec;
+        out->n_exceptions = n_exc;
+        out->status = status;
+        out->reserved = 0;
+    }
 }
 
-hipError_t launch_finalize(const Launch& L, void* out_summaries, void* out_records,
+hipError_t launch_finalize(const Launch& L, const Acc* accs, void* out_summaries, void* out_records,
                            uint64_t* out_exceptions, uint64_t exc_cap, hipStream_t s)
 {
     if (L.n_iv == 0)
         return hipSuccess;
     const size_t lds = out_exceptions ? (size_t)kFinalizeSortCap * 8 : 0;
-    hipLaunchKernelGGL(k_finalize, dim3(L.n_iv), dim3(out_exceptions ? 1024 : 64), lds, s, L,
-                       out_summaries, out_records, out_exceptions, exc_cap);
+    hipLaunchKernelGGL(k_finalize, dim3(L.n_iv), dim3(out_exceptions ? 1024 : 256), lds, s, L, accs,
+                       out_summaries, out_records, out_exceptions, exc_cap, tail_in_finalize(L) ? 1 : 0);
     return hipGetLastError();
 }
 
