@@ -440,14 +440,6 @@ uint32_t medium_end(const Ctx* c, const Params& par)
     return std::min<uint32_t>(e, kFirstMedium + (uint32_t)kMaxMedium);
 }
 
-// Threads per workgroup of the segment kernel in a mode (0 summary, 1 per-n,
-// 2 sieve alone) for a launch of n_iv intervals: per-n batches of many (short)
-// intervals keep the summary block size, which keeps more workgroups resident.
-uint32_t block_for(const Params& par, int mode, uint32_t n_iv)
-{
-    return (uint32_t)(mode == 2 ? par.sieve_block : mode == 1 && n_iv == 1 ? par.per_n_block : par.block);
-}
-
 // Segment geometry of a launch: S odd numbers per segment, the region's words
 // around them, and the segment kernel's mode.
 struct Geometry {
@@ -455,27 +447,32 @@ struct Geometry {
     bool col;
 };
 
-// mode 0 verify, 1 per-n, 2 sieve alone; klds the deepest step searched in LDS.
-// The halo below a segment holds the candidates of depth up to kh, also when
-// kmax is smaller (a larger halo is harmless): the geometry, and with it the
-// medium-prime tables, depends on the knobs only.
+// mode 0 verify, 1 per-n, 2 sieve alone; klds the deepest step searched in LDS;
+// log2S the segment length.  The halo below a segment holds the candidates of
+// depth up to kh, also when kmax is smaller (a larger halo is harmless): the
+// geometry, and with it the medium-prime tables, depends on the knobs and the
+// segment length only.
 // Summary mode takes the column layout (k_column) at the segment length, halo
 // (kh = 13) and block size that its one instance is compiled for, where the
 // search goes past the four steps that it runs without a level bound.
-Geometry geometry(const Params& par, int mode, uint32_t klds)
+bool column_layout(const Params& par, int mode, uint32_t klds)
+{
+    return mode == 0 && klds >= 5 && par.kh == 13 && par.seg_log2 == kColLog2 && par.block == (int)kColBlock;
+}
+
+Geometry geometry(const Params& par, int mode, uint32_t klds, int log2S)
 {
     Geometry g;
     std::memset(&g, 0, sizeof(g));
     g.kmode = (uint32_t)mode;
+    g.S = 1u << log2S;
     if (mode == 2) {
         g.hup = 1;
-        g.S = 1u << par.sieve_seg_log2;
     } else {
         g.hlo = (par.kh >= 7 ? (1u << (par.kh - 1)) : 64u) / 64;
-        g.S = 1u << par.seg_log2;
-        g.col = mode == 0 && klds >= 5 && g.hlo * 64 == kColHalo && par.seg_log2 == kColLog2 &&
-                par.block == (int)kColBlock;
+        g.col = column_layout(par, mode, klds);
         if (g.col) {
+            static_assert(kColHalo == 1u << 12, "the halo at kh = 13");
             g.kmode = 3;
             g.S = (1u << kColLog2) - kColHalo;
             g.rw = (1u << kColLog2) / 64;
@@ -486,22 +483,57 @@ Geometry geometry(const Params& par, int mode, uint32_t klds)
     return g;
 }
 
+// Segment length of a launch over n numbers in n_iv intervals: the knob's, or,
+// where that is the default and leaves most of the chip idle, the longest that
+// still makes this many segments (one interval: 128, the sieve alone 64;
+// several: 512), down to 2^14.  2^21 odd n per-n: 18.7 us in 8 segments of
+// 2^18, 14.6 in 128; 2^20 odd m sieved: 9.7 us in one segment, 6 in 64; past
+// these counts shorter segments gain nothing (their halo, tables and starts
+// grow).
+int seg_log2_for(const Params& par, int mode, uint32_t klds, uint64_t n, uint32_t n_iv)
+{
+    const Params dflt;
+    const int knob = mode == 2 ? par.sieve_seg_log2 : par.seg_log2;
+    if (knob != (mode == 2 ? dflt.sieve_seg_log2 : dflt.seg_log2) || column_layout(par, mode, klds))
+        return knob;
+    const uint64_t wanted = n_iv > 1 ? 512 : mode == 2 ? 64 : 128;
+    int s = knob;
+    while (s > kShortSegLog2 && (n >> s) < wanted)
+        s--;
+    return s;
+}
+
+// Threads per workgroup of the segment kernel in a mode (0 summary, 1 per-n,
+// 2 sieve alone) for a launch of n_iv intervals: per-n batches of many (short)
+// intervals keep the summary block size, which keeps more workgroups resident;
+// segments too short for it take no more than 512.
+uint32_t block_for(const Params& par, int mode, uint32_t n_iv, int log2S)
+{
+    const int b = mode == 2 ? par.sieve_block : mode == 1 && n_iv == 1 ? par.per_n_block : par.block;
+    const int knob = mode == 2 ? par.sieve_seg_log2 : par.seg_log2;
+    return (uint32_t)(log2S < knob && log2S <= (mode == 2 ? 17 : 16) ? std::min(b, 512) : b);
+}
+
 // The medium-prime tables of the verify geometries for the current knobs
-// (summary, per-n, and summary with a bounded search), made at set-up
-// (esq_init, esq_set_param; g_mu held) so that calls find them resident.
+// (summary, per-n, and summary with a bounded search, at every segment length
+// that seg_log2_for may take), made at set-up (esq_init, esq_set_param; g_mu
+// held) so that calls find them resident.
 int prebuild_med_table(Ctx* c, const Params& par)
 {
+    const uint32_t med_end = medium_end(c, par);
+    if (med_end <= kFirstMedium)
+        return ESQ_OK;
     MedTable* mt = nullptr;
     for (int v = 0; v < 3; v++) {
         const int mode = v == 1 ? 1 : 0;
-        const Geometry g = geometry(par, mode, v == 2 ? 1u : (uint32_t)par.kh);
-        const uint32_t med_end = medium_end(c, par);
-        if (med_end <= kFirstMedium)
-            continue;
-        const int rc = get_med_table_locked(c, g.rw, g.S, g.col, med_end, (uint32_t)par.entry_hits,
-                                            block_for(par, mode, 1), &mt);
-        if (rc)
-            return rc;
+        const uint32_t klds = v == 2 ? 1u : (uint32_t)par.kh;
+        for (int s = seg_log2_for(par, mode, klds, 0, 1); s <= par.seg_log2; s++) {
+            const Geometry g = geometry(par, mode, klds, s);
+            const int rc = get_med_table_locked(c, g.rw, g.S, g.col, med_end, (uint32_t)par.entry_hits,
+                                                block_for(par, mode, 1, s), &mt);
+            if (rc)
+                return rc;
+        }
     }
     return ESQ_OK;
 }
@@ -543,10 +575,14 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
          bool exc_list, Planned* P, bool no_alloc = false)
 {
     const uint32_t n_iv = (uint32_t)reqs.size();
-    const uint32_t blk = block_for(par, mode, n_iv);
     const uint32_t kmax_eff = kmax ? kmax : 63;
     const uint32_t klds = std::min<uint32_t>(kmax_eff, (uint32_t)par.kh);
-    const Geometry geo = geometry(par, mode, klds);
+    uint64_t n_all = 0;
+    for (const Req& r : reqs)
+        n_all += r.I1 > r.I0 ? r.I1 - r.I0 : 0;
+    const int log2S = seg_log2_for(par, mode, klds, n_all, n_iv);
+    const Geometry geo = geometry(par, mode, klds, log2S);
+    const uint32_t blk = block_for(par, mode, n_iv, log2S);
     const uint64_t S = geo.S;
     const uint32_t SW = (uint32_t)(S / 64);
     const uint32_t hlo = geo.hlo, hup = geo.hup, rw = geo.rw;
@@ -825,7 +861,7 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     P->bytes = off;
 
     Launch& L = P->L;
-    std::memset(&L, 0, sizeof(L));
+    L = Launch();
     L.S = (uint32_t)S;
     L.s_inv = ~0ull / S;
     L.hlo_words = hlo;
@@ -890,6 +926,8 @@ void bind(Planned* P, char* base)
     for (size_t i = 0; i < P->ivs.size(); i++)
         P->ivs[i].acc = accs + i;
     L.iv = (const Interval*)(base + P->o_iv);
+    if (P->ivs.size() == 1)
+        L.iv0 = P->ivs[0];
     L.items = P->items.empty() ? nullptr : (const uint4*)(base + P->o_items);
     L.bucket_cnt = P->any_bucket ? (uint32_t*)(base + P->o_bcnt) : nullptr;
     L.bucket_slot = P->any_bucket ? (uint32_t*)(base + P->o_bslot) : nullptr;
@@ -1395,10 +1433,13 @@ int esq_scratch_bytes(uint32_t count, const uint64_t* lo, const uint64_t* hi, ui
     bool per_n = false;
     if ((rc = make_batch_reqs(c, count, lo, hi, nullptr, &reqs, &per_n)))
         return rc;
-    Planned P;
-    if ((rc = plan(c, par, 0, kmax, reqs, false, &P)))
-        return rc;
-    *out_bytes = P.bytes;
+    // summary and per-n launches may differ in segment length: the larger
+    for (int mode = 0; mode < 2; mode++) {
+        Planned P;
+        if ((rc = plan(c, par, mode, kmax, reqs, false, &P)))
+            return rc;
+        *out_bytes = std::max<uint64_t>(*out_bytes, P.bytes);
+    }
     return ESQ_OK;
 }
 

@@ -52,6 +52,7 @@ constexpr unsigned long long kNone = ~0ull;
 constexpr int kMaxSegLog2 = 20;
 constexpr uint32_t kFlushSegs = 4096;     // segments per run and per flush of partial totals
 constexpr int kMinSegLog2 = 10;
+constexpr int kShortSegLog2 = 14;         // shortest segment of a short launch at the default knobs
 constexpr uint32_t kFinalizeSortCap = 16384;  // LDS sort capacity of the finalize pass
 constexpr uint32_t kOwnSegs = 256;        // segments per workgroup of k_bucket_own, at most
 constexpr uint64_t kCofactorPrime = 1u << 20; // largest direct/cofactor cut-over considered
@@ -106,7 +107,8 @@ struct Launch {
     uint32_t bucket_cap;          // hit slots per segment
     uint32_t nprimes;
     const Interval* iv;
-    const uint4* items;           // (interval, first segment, segments, 0), or null
+    Interval iv0;                 // one interval: its descriptor
+    const uint4* items;           // (interval, first segment, segments, 0), or null: one interval
     const uint32_t* primes;       // odd primes ascending
     const uint32_t* pbits;        // bit i: 2 i + 1 is prime, for the odd numbers up to plimit
     uint32_t plimit;

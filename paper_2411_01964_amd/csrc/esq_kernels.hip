@@ -680,6 +680,24 @@ __device__ __forceinline__ void stage_store_run(u32x4* st, g_u8* out, const uint
         store_part16(g + 4096, stage_shift<KQ>(last, last, sh), 0, delta);
 }
 
+// Run `it` of a launch over one interval of ns segments: the first `grid` runs
+// are run_long segments each, the rest of the segments is cut into runs of
+// run_short; or, with run_long = 0, n_items equal runs.
+__device__ __forceinline__ void run_of(uint32_t it, uint32_t ns, uint32_t n_items, uint32_t run_long,
+                                       uint32_t run_short, uint32_t grid, uint32_t* first, uint32_t* n)
+{
+    if (run_long == 0) {
+        *first = (uint32_t)((uint64_t)it * ns / n_items);
+        *n = (uint32_t)((uint64_t)(it + 1) * ns / n_items) - *first;
+    } else if (it < grid) {
+        *first = it * run_long;
+        *n = run_long;
+    } else {
+        *first = grid * run_long + (it - grid) * run_short;
+        *n = min(run_short, ns - *first);
+    }
+}
+
 // LDS layout of k_verify: the region bitmap (rw words), a control block of
 // kVerifyCtrlWords words (per-item first-n slots, level counts, the item,
 // phase-clock sums), then the medium primes' (q, S mod q), their current
@@ -733,7 +751,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
     uint32_t acc_segs = 0;    // segments in the partial totals
     auto flush = [&](uint32_t iv) {
         if (MODE != 2) {
-            Acc* acc = L.iv[iv].acc;
+            Acc* acc = L.items ? L.iv[iv].acc : L.iv0.acc;
 #pragma unroll
             for (int k = 1; k <= kRegLevels; k++) {
                 if (k > (int)klds)
@@ -777,26 +795,24 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
             __builtin_amdgcn_s_sleep(1);
     }
 
+    // Work items.  The first is the workgroup's own number, the others come
+    // from the queue (a device-scope operation of a microsecond, and of ten
+    // when all workgroups start with one), if there are more than workgroups.
+    bool first_item = true;
     for (;;) {
         if (tid == 0) {
-            uint32_t ok = 0, ivi = 0, b = 0, cnt = 0;
-            if (L.items) {
-                const uint32_t it = atomicAdd(L.queue, 1u);
-                if (it < L.n_items) {
+            uint32_t ok = 0, ivi = 0, b = 0, cnt = 0, it = blockIdx.x;
+            if (!first_item)
+                it = L.n_items > gridDim.x ? gridDim.x + atomicAdd(L.queue, 1u) : ~0u;
+            if (it < L.n_items) {
+                ok = 1;
+                if (L.items) {
                     const uint4 x = L.items[it];
-                    ok = 1;
                     ivi = x.x;
                     b = x.y;
                     cnt = x.z;
-                }
-            } else {
-                // one interval: run `it` of L.n_items equal runs
-                const uint32_t it = atomicAdd(L.queue, 1u);
-                if (it < L.n_items) {
-                    const uint64_t ns = L.iv[0].nseg;
-                    ok = 1;
-                    b = (uint32_t)((uint64_t)it * ns / L.n_items);
-                    cnt = (uint32_t)((uint64_t)(it + 1) * ns / L.n_items) - b;
+                } else {
+                    run_of(it, L.iv0.nseg, L.n_items, L.run_long, L.run_short, gridDim.x, &b, &cnt);
                 }
             }
             s_item[0] = ivi;
@@ -804,6 +820,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
             s_item[2] = cnt;
             s_item[3] = ok;
         }
+        first_item = false;
         __syncthreads();
         const uint32_t item_ok = rfl(s_item[3]);
         const uint32_t ivi = rfl(s_item[0]), seg0 = rfl(s_item[1]), nsegs = rfl(s_item[2]);
@@ -834,7 +851,9 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
             __syncthreads();
         }
         acc_segs += nsegs;
-        const Interval IV = L.iv[ivi];
+        // (scalar loads, from the kernel's arguments for one interval)
+        CInterval& IV = *(L.items ? (CInterval*)(uintptr_t)(L.iv + ivi)
+                                  : &((const __attribute__((address_space(4))) Launch*)__builtin_amdgcn_kernarg_segment_ptr())->iv0);
         const uint32_t cap = L.bucket_cap;
         // The issue arbiter favours older waves, so of the workgroups sharing
         // a CU the first-launched would finish far ahead of the last.  Raising
@@ -1410,24 +1429,6 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
     }
 }
 
-// Run `it` of a launch over one interval of ns segments: the first `grid` runs
-// are run_long segments each, the rest of the segments is cut into runs of
-// run_short; or, with run_long = 0, n_items equal runs.
-__device__ __forceinline__ void run_of(uint32_t it, uint32_t ns, uint32_t n_items, uint32_t run_long,
-                                       uint32_t run_short, uint32_t grid, uint32_t* first, uint32_t* n)
-{
-    if (run_long == 0) {
-        *first = (uint32_t)((uint64_t)it * ns / n_items);
-        *n = (uint32_t)((uint64_t)(it + 1) * ns / n_items) - *first;
-    } else if (it < grid) {
-        *first = it * run_long;
-        *n = run_long;
-    } else {
-        *first = grid * run_long + (it - grid) * run_short;
-        *n = min(run_short, ns - *first);
-    }
-}
-
 // Summary mode in the column layout (see esq_internal.h): regions of 2^kColLog2
 // bits by workgroups of kColBlock threads, four of them on a CU.
 //
@@ -1457,7 +1458,6 @@ __global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(8))) 
     // change from segment to segment: kept in registers they do not fit, and
     // spilled scalars cost a vector instruction each.
     typedef const __attribute__((address_space(4))) Launch CLaunch;
-    typedef const __attribute__((address_space(4))) Interval CInterval;
     CLaunch* lp = (CLaunch*)__builtin_amdgcn_kernarg_segment_ptr();
     (void)Larg;
 
@@ -1496,7 +1496,7 @@ __global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(8))) 
     uint32_t cur_iv = ~0u, acc_segs = 0;
     auto flush = [&](uint32_t iv) {
         asm volatile("" : "+s"(lp));
-        Acc* acc = lp->iv[iv].acc;
+        Acc* acc = lp->items ? lp->iv[iv].acc : lp->iv0.acc;
         const uint32_t klds = lp->k_lds;
 #pragma unroll
         for (int k = 1; k <= kRegLevels; k++) {
@@ -1542,7 +1542,7 @@ __global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(8))) 
                     b = x.y;
                     n = x.z;
                 } else {
-                    run_of(it, lp->iv[0].nseg, lp->n_items, lp->run_long, lp->run_short, gridDim.x, &b, &n);
+                    run_of(it, lp->iv0.nseg, lp->n_items, lp->run_long, lp->run_short, gridDim.x, &b, &n);
                 }
             }
             s_item[0] = ivi;
@@ -1577,7 +1577,7 @@ __global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(8))) 
             __syncthreads();
         }
         acc_segs += nsegs;
-        CInterval* ivp = (CInterval*)(uintptr_t)(lp->iv + ivi);
+        CInterval* ivp = lp->items ? (CInterval*)(uintptr_t)(lp->iv + ivi) : &lp->iv0;
         // n-index of region position 0's slot: slot y is n-index nh + y, its
         // k-th candidate position y - (2^(k-1) - 1), position 0 odd index nh - 1
         int64_t nh = ivp->A0 + (int64_t)seg0 * (int64_t)S - (int64_t)H;
