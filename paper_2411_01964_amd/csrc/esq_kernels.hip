@@ -723,11 +723,19 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
     uint64_t* bm = lds;
     uint32_t* bm32 = reinterpret_cast<uint32_t*>(bm);
     constexpr uint32_t kCntAt = kMaxKh + 2, kItemAt = kCntAt + (kMaxKh + 2) / 2, kPhAt = kItemAt + 2;
-    static_assert(kPhAt + 3 <= kVerifyCtrlWords, "k_verify control block");
+    constexpr uint32_t kNTailAt = kPhAt + 3, kTailAt = kNTailAt + 1;
+    static_assert(kTailAt + kTailList <= kVerifyCtrlWords, "k_verify control block");
     unsigned long long* s_first = reinterpret_cast<unsigned long long*>(lds + L.rw);  // kMaxKh + 2
     uint32_t* s_cnt = reinterpret_cast<uint32_t*>(lds + L.rw + kCntAt);               // kMaxKh + 1
     uint32_t* s_item = reinterpret_cast<uint32_t*>(lds + L.rw + kItemAt);             // 4
     unsigned long long* s_ph = reinterpret_cast<unsigned long long*>(lds + L.rw + kPhAt);  // 3 (phase clock)
+    // the segment's n that go to the tail pass or the list of exceptions
+    uint32_t* s_ntail = reinterpret_cast<uint32_t*>(lds + L.rw + kNTailAt);
+    unsigned long long* s_tail = reinterpret_cast<unsigned long long*>(lds + L.rw + kTailAt);  // kTailList
+    if (tid == 0) {
+        s_ntail[0] = 0;
+        s_ntail[1] = kTailList;
+    }
     uint2* s_medq = reinterpret_cast<uint2*>(lds + L.rw + kVerifyCtrlWords);
     uint32_t* s_f = reinterpret_cast<uint32_t*>(s_medq + nmed);
     uint2* s_task = reinterpret_cast<uint2*>(lds + L.rw + kVerifyCtrlWords + nmed + (nmed + 1) / 2);
@@ -1231,6 +1239,16 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
             const uint32_t iters = (SW + T - 1) / T;
             // STEADY: the least n of depth 2 .. 5 have been offered already, so
             // steps 1 .. 4 run without any branch.
+            const bool no_tail = klds >= L.kmax_eff;
+            auto push_tail = [&](uint64_t j, unsigned long long idx) {
+                if (idx < L.tail_cap) {
+                    L.tail_n[idx] = j;
+                    L.tail_iv[idx] = ivi;
+                } else {
+                    g_or(&IV.acc->status, no_tail ? (unsigned)ESQ_STATUS_EXCEPTIONS_INCOMPLETE
+                                                  : (unsigned)ESQ_STATUS_TAIL_OVERFLOW);
+                }
+            };
             const uint64_t* pbase = bm + HW + tid - 1;  // FAST: word before pass 0's word
             auto word_pass = [&](auto fast_c, auto steady_c, uint32_t itw) {
                 constexpr bool FAST = decltype(fast_c)::value;
@@ -1346,22 +1364,24 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
                 // pass -- unless the search limit is the in-LDS depth, so that
                 // these n are exceptions already counted in cnt[k_lds]; then
                 // they are listed only when the call lists exceptions
-                const bool no_tail = klds >= L.kmax_eff;
                 if (__builtin_expect(alive, 0) && U && (!no_tail || L.exc_list)) {
-                    // one reservation of popcount(U) list entries per word
+                    // one reservation of popcount(U) entries per word, in the
+                    // list's memory once the segment's is full
                     const uint64_t j0 = j0_of();
-                    const unsigned long long c = (unsigned long long)__popcll(U);
-                    unsigned long long idx = atomicAdd(L.tail_count, c);
-                    for (uint64_t x = U; x; idx++) {
-                        const int bit = __ffsll((unsigned long long)x) - 1;
-                        x &= x - 1;
-                        if (idx < L.tail_cap) {
-                            L.tail_n[idx] = j0 + (uint64_t)bit;
-                            L.tail_iv[idx] = ivi;
-                        } else {
-                            g_or(&IV.acc->status, no_tail ? (unsigned)ESQ_STATUS_EXCEPTIONS_INCOMPLETE
-                                                              : (unsigned)ESQ_STATUS_TAIL_OVERFLOW);
-                        }
+                    const uint32_t c = (uint32_t)__popcll(U);
+                    uint32_t at = atomicAdd(&s_ntail[0], c);
+                    const bool here = at + c <= kTailList;
+                    unsigned long long idx = 0;
+                    if (!here) {
+                        atomicMin(&s_ntail[1], at);  // the segment's entries end here
+                        idx = atomicAdd(L.tail_count, (unsigned long long)c);
+                    }
+                    for (uint64_t x = U; x; x &= x - 1, at++, idx++) {
+                        const uint64_t j = j0 + (uint64_t)(__ffsll((unsigned long long)x) - 1);
+                        if (here)
+                            s_tail[at] = j;
+                        else
+                            push_tail(j, idx);
                     }
                 }
                 if (MODE == 1 && IV.out_mink) {
@@ -1421,6 +1441,23 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
                     word_pass(std::false_type{}, std::false_type{}, itw);
             }
             __syncthreads();
+            // the segment's listed n, with one reservation (a device-scope
+            // operation each bounded a search that lists 2400 exceptions);
+            // reset two barriers before the next search
+            if (tid < 64) {
+                const uint32_t m = rfl(min(s_ntail[0], s_ntail[1]));
+                if (m) {
+                    unsigned long long base = 0;
+                    if (lane == 0) {
+                        base = atomicAdd(L.tail_count, (unsigned long long)m);
+                        s_ntail[0] = 0;
+                        s_ntail[1] = kTailList;
+                    }
+                    base = __shfl(base, 0);
+                    if (lane < m)
+                        push_tail(s_tail[lane], base + lane);
+                }
+            }
             phase_tick(2);
         }
 
