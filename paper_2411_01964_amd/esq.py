@@ -55,6 +55,7 @@ class Record(ctypes.Structure):
 
 
 SUMMARY_BYTES = ctypes.sizeof(Summary)
+_FIXED_BYTES = SUMMARY_BYTES + ESQ_RECORDS_CAP * ctypes.sizeof(Record)
 PER_N_SLAB = 544 << 20   # per-n output slab of a batch: any interval of up to 2^29 odd n fits
 RECORD_BYTES = ctypes.sizeof(Record)
 
@@ -240,11 +241,12 @@ class Pending:
         n0 = max(self.lo, 3) | 1
         self.n_odd = (self.hi - n0 + 1) // 2 if self.hi > n0 else 0
         dev = torch.device("cuda", torch.cuda.current_device())
-        self.summary = torch.empty(SUMMARY_BYTES, dtype=torch.uint8, device=dev)
-        self.records = torch.empty(ESQ_RECORDS_CAP * RECORD_BYTES, dtype=torch.uint8, device=dev)
         self.exc_cap = int(exceptions_cap)
-        self.exceptions = (torch.empty(self.exc_cap, dtype=torch.int64, device=dev)
-                           if self.exc_cap else None)
+        # one buffer, so that result() takes one copy: summary, records, exceptions
+        self._out = torch.empty(_FIXED_BYTES + 8 * max(self.exc_cap, 0), dtype=torch.uint8, device=dev)
+        self.summary = self._out[:SUMMARY_BYTES]
+        self.records = self._out[SUMMARY_BYTES:_FIXED_BYTES]
+        self.exceptions = self._out[_FIXED_BYTES:].view(torch.int64) if self.exc_cap else None
         self.per_n = _per_n_buffer(n0, self.n_odd, dev) if per_n else None
         self.stream = stream if stream is not None else torch.cuda.current_stream()
         call = lib().esq_verify_range_noalloc if noalloc else lib().esq_verify_range
@@ -259,34 +261,17 @@ class Pending:
         return self.event.query()
 
     def result(self, check: bool = True) -> dict:
-        self.event.synchronize()
-        s = Summary.from_buffer_copy(bytes(self.summary.cpu().numpy().tobytes()))
-        recs_raw = self.records.cpu().numpy().tobytes()
-        nrec = min(s.n_records, ESQ_RECORDS_CAP)
-        recs, flags = [], []
-        for i in range(nrec):
-            r = Record.from_buffer_copy(recs_raw[i * RECORD_BYTES:(i + 1) * RECORD_BYTES])
-            recs.append((int(r.n), int(r.k)))
-            flags.append(int(r.flags))
-        nexc = min(int(s.n_exceptions), self.exc_cap)
-        exc = [int(x) for x in self.exceptions[:nexc].cpu().tolist()] if nexc else []
-        out = {
-            "n0": int(s.n0),
-            "n_odd": int(s.n_odd),
-            "hist": [int(x) for x in s.hist],
-            "ksum": int(s.ksum),
-            "kmax_seen": int(s.kmax_seen),
-            "n_records": int(s.n_records),
-            "records": recs,
-            "record_flags": flags,
-            "n_exceptions": int(s.n_exceptions),
-            "exceptions": exc,
-            "status": int(s.status),
-        }
+        # a copy on the call's own stream waits for the call by itself
+        if torch.cuda.current_stream() != self.stream:
+            self.event.synchronize()
+        raw = self._out.cpu().numpy()
+        out = _parse(raw[:SUMMARY_BYTES], raw[SUMMARY_BYTES:_FIXED_BYTES])
+        nexc = min(out["n_exceptions"], self.exc_cap)
+        out["exceptions"] = raw[_FIXED_BYTES:_FIXED_BYTES + 8 * nexc].view("<i8").tolist() if nexc else []
         if self.per_n is not None:
             out["per_n"] = self.per_n[:self.n_odd]
-        if check and s.status:
-            raise EsqError(-100, "device status 0x%x for [%d, %d)" % (s.status, self.lo, self.hi))
+        if check and out["status"]:
+            raise EsqError(-100, "device status 0x%x for [%d, %d)" % (out["status"], self.lo, self.hi))
         return out
 
 
@@ -310,22 +295,18 @@ def verify_range(lo, hi, kmax=0, per_n=False, exceptions_cap=0, stream=None, che
 def _parse(summary_bytes, record_bytes):
     s = Summary.from_buffer_copy(summary_bytes)
     nrec = min(s.n_records, ESQ_RECORDS_CAP)
-    recs, flags = [], []
-    for i in range(nrec):
-        r = Record.from_buffer_copy(record_bytes[i * RECORD_BYTES:(i + 1) * RECORD_BYTES])
-        recs.append((int(r.n), int(r.k)))
-        flags.append(int(r.flags))
+    recs = (Record * nrec).from_buffer_copy(record_bytes)
     return {
-        "n0": int(s.n0),
-        "n_odd": int(s.n_odd),
-        "hist": [int(x) for x in s.hist],
-        "ksum": int(s.ksum),
-        "kmax_seen": int(s.kmax_seen),
-        "n_records": int(s.n_records),
-        "records": recs,
-        "record_flags": flags,
-        "n_exceptions": int(s.n_exceptions),
-        "status": int(s.status),
+        "n0": s.n0,
+        "n_odd": s.n_odd,
+        "hist": list(s.hist),
+        "ksum": s.ksum,
+        "kmax_seen": s.kmax_seen,
+        "n_records": s.n_records,
+        "records": [(r.n, r.k) for r in recs],
+        "record_flags": [r.flags for r in recs],
+        "n_exceptions": s.n_exceptions,
+        "status": s.status,
     }
 
 
@@ -363,9 +344,10 @@ class PendingBatch:
             raise ValueError("lo and hi must be 1-D of equal length")
         self.count = int(self.lo.size)
         dev = torch.device("cuda", torch.cuda.current_device())
-        self.summaries = torch.empty(max(self.count, 1) * SUMMARY_BYTES, dtype=torch.uint8, device=dev)
-        self.records = torch.empty(max(self.count, 1) * ESQ_RECORDS_CAP * RECORD_BYTES,
-                                   dtype=torch.uint8, device=dev)
+        # one buffer, so that result() takes one copy: summaries, records
+        self._out = torch.empty(max(self.count, 1) * _FIXED_BYTES, dtype=torch.uint8, device=dev)
+        self.summaries = self._out[:max(self.count, 1) * SUMMARY_BYTES]
+        self.records = self._out[max(self.count, 1) * SUMMARY_BYTES:]
         self.per_n = None
         ptrs = None
         if per_n is not None and any(per_n):
@@ -427,8 +409,11 @@ class PendingBatch:
         return self.event.query()
 
     def result(self, check: bool = True) -> list:
-        self.event.synchronize()
-        out = _parse_many(self.summaries, self.records, self.count)
+        # a copy on the batch's own stream waits for the batch by itself
+        if torch.cuda.current_stream() != self.stream:
+            self.event.synchronize()
+        raw = self._out.cpu()
+        out = _parse_many(raw[:self.summaries.numel()], raw[self.summaries.numel():], self.count)
         for i, r in enumerate(out):
             if self.per_n is not None and self.per_n[i] is not None:
                 r["per_n"] = self.per_n[i]
