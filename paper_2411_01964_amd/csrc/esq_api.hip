@@ -161,12 +161,17 @@ struct Staging {
 std::mutex g_stage_mu;
 std::vector<Staging> g_stage;
 
-int stage_upload(const std::vector<std::pair<const void*, size_t>>& parts,
-                 const std::vector<char*>& dsts, hipStream_t s)
+// The parts (pointer, bytes) to dst + their offsets, in one copy.
+struct UploadPart {
+    const void* from;
+    size_t bytes, at;
+};
+
+int stage_upload(const std::vector<UploadPart>& parts, char* dst, hipStream_t s)
 {
     size_t total = 0;
     for (auto& p : parts)
-        total += (p.second + 255) & ~(size_t)255;
+        total = std::max(total, p.at + p.bytes);
     if (total == 0)
         return ESQ_OK;
     int idx = -1;
@@ -199,18 +204,12 @@ int stage_upload(const std::vector<std::pair<const void*, size_t>>& parts,
         std::lock_guard<std::mutex> lk(g_stage_mu);
         st = g_stage[idx];
     }
-    size_t off = 0;
     int rc = ESQ_OK;
-    for (size_t i = 0; i < parts.size(); i++) {
-        std::memcpy((char*)st.host + off, parts[i].first, parts[i].second);
-        hipError_t e = hipMemcpyAsync(dsts[i], (char*)st.host + off, parts[i].second,
-                                      hipMemcpyHostToDevice, s);
-        if (e != hipSuccess) {
-            rc = hip_fail(e, "hipMemcpyAsync(descriptors)");
-            break;
-        }
-        off += (parts[i].second + 255) & ~(size_t)255;
-    }
+    for (auto& p : parts)
+        std::memcpy((char*)st.host + p.at, p.from, p.bytes);
+    hipError_t e = hipMemcpyAsync(dst, st.host, total, hipMemcpyHostToDevice, s);
+    if (e != hipSuccess)
+        rc = hip_fail(e, "hipMemcpyAsync(descriptors)");
     (void)hipEventRecord(st.done, s);
     std::lock_guard<std::mutex> lk(g_stage_mu);
     g_stage[idx].taken = false;
@@ -838,14 +837,15 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
 
     // scratch layout, one allocation
     size_t off = 0;
+    // (the uploaded descriptors first and together: one copy)
     P->o_iv = off;
     off = align_up(off + sizeof(Interval) * std::max<uint32_t>(n_iv, 1));
-    P->o_acc = off;
-    off = align_up(off + sizeof(Acc) * std::max<uint32_t>(n_iv, 1));
     P->o_items = off;
     off = align_up(off + sizeof(uint4) * items.size());
     P->o_ranges = off;
     off = align_up(off + sizeof(uint4) * P->ranges.size());
+    P->o_acc = off;
+    off = align_up(off + sizeof(Acc) * std::max<uint32_t>(n_iv, 1));
     P->o_bcnt = off;
     off = align_up(off + (any_bucket ? nseg_total * 4 : 0));
     P->o_bslot = off;
@@ -939,19 +939,19 @@ void bind(Planned* P, char* base)
 }
 
 // The kernels of one launch, in stream order (no allocation, no copy): this
-// is what a hipGraph captures.  With iv_by_value the single interval's
-// descriptor travels as a kernel argument instead of being uploaded.
-int launch_seq(const Planned& P, bool iv_by_value, bool profile, void* out_summaries,
+// is what a hipGraph captures.  A single interval's descriptor travels as a
+// kernel argument instead of being uploaded.
+int launch_seq(const Planned& P, bool profile, void* out_summaries,
                void* out_records, uint64_t* out_exceptions, uint64_t exc_cap, hipStream_t s)
 {
     const Launch& L = P.L;
     Acc* accs = P.ivs.empty() ? nullptr : P.ivs[0].acc;
     hipError_t e;
     int rc;
-    if ((e = launch_prepare(L, accs, iv_by_value ? &P.ivs[0] : nullptr,
-                            P.n_ranges ? 0u : (uint32_t)P.nseg_total, s)) != hipSuccess)
+    // k_bucket_own clears what k_prepare does
+    if (!P.n_ranges && (e = launch_prepare(L, accs, (uint32_t)P.nseg_total, s)) != hipSuccess)
         return hip_fail(e, "k_prepare");
-    if (P.any_bucket && (e = launch_bucket(L, P.n_heavy, P.max_direct, P.max_cof, P.p_cof, P.in_doubles,
+    if (P.any_bucket && (e = launch_bucket(L, accs, P.n_heavy, P.max_direct, P.max_cof, P.p_cof, P.in_doubles,
                                            P.ranges.empty() ? nullptr : (const uint4*)(P.base + P.o_ranges), P.n_ranges,
                                            s)) != hipSuccess)
         return hip_fail(e, "k_bucket");
@@ -1063,24 +1063,17 @@ int enqueue(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vecto
     bind(&P, base);
     const bool by_value = P.ivs.size() == 1;
     if (!by_value) {
-        std::vector<std::pair<const void*, size_t>> parts;
-        std::vector<char*> dsts;
-        parts.push_back({P.ivs.data(), sizeof(Interval) * P.ivs.size()});
-        dsts.push_back(base + P.o_iv);
-        if (!P.items.empty()) {
-            parts.push_back({P.items.data(), sizeof(uint4) * P.items.size()});
-            dsts.push_back(base + P.o_items);
-        }
-        if (!P.ranges.empty()) {
-            parts.push_back({P.ranges.data(), sizeof(uint4) * P.ranges.size()});
-            dsts.push_back(base + P.o_ranges);
-        }
-        if ((rc = stage_upload(parts, dsts, s))) {
+        const std::vector<UploadPart> parts = {
+            {P.ivs.data(), sizeof(Interval) * P.ivs.size(), P.o_iv},
+            {P.items.data(), sizeof(uint4) * P.items.size(), P.o_items},
+            {P.ranges.data(), sizeof(uint4) * P.ranges.size(), P.o_ranges},
+        };
+        if ((rc = stage_upload(parts, base, s))) {
             release();
             return rc;
         }
     }
-    rc = launch_seq(P, by_value, par.profile != 0, out_summaries, out_records, out_exceptions,
+    rc = launch_seq(P, par.profile != 0, out_summaries, out_records, out_exceptions,
                     exc_cap, s);
     release();
     return rc;
@@ -1383,7 +1376,7 @@ int esq_verify_range_noalloc(uint64_t lo, uint64_t hi, uint32_t kmax, uint8_t* d
     bind(&P, base);
     // the single interval's descriptor travels as a kernel argument: no
     // upload, no staging buffer; no profiling events either
-    return launch_seq(P, true, false, out_summary, out_records,
+    return launch_seq(P, false, out_summary, out_records,
                       exc_list ? out_exceptions : nullptr, exceptions_cap, (hipStream_t)stream);
 }
 
@@ -1514,7 +1507,7 @@ int esq_batch_launch(esq_batch* b, int use_graph, void* stream)
         return hip_fail(e, "hipSetDevice");
     hipStream_t s = (hipStream_t)stream;
     if (!use_graph)
-        return launch_seq(b->P, false, b->profile, b->out_summaries, b->out_records, nullptr, 0, s);
+        return launch_seq(b->P, b->profile, b->out_summaries, b->out_records, nullptr, 0, s);
     if (!b->exec) {
         // capture on a private stream (the legacy default stream cannot be
         // captured); the instantiated graph is launched on the caller's stream
@@ -1523,7 +1516,7 @@ int esq_batch_launch(esq_batch* b, int use_graph, void* stream)
             return hip_fail(e, "hipStreamCreate(capture)");
         if ((e = hipStreamBeginCapture(b->capture, hipStreamCaptureModeThreadLocal)) != hipSuccess)
             return hip_fail(e, "hipStreamBeginCapture");
-        int rc = launch_seq(b->P, false, false, b->out_summaries, b->out_records, nullptr, 0,
+        int rc = launch_seq(b->P, false, b->out_summaries, b->out_records, nullptr, 0,
                             b->capture);
         hipGraph_t g = nullptr;
         e = hipStreamEndCapture(b->capture, &g);

@@ -140,9 +140,8 @@ struct Launch {
 // launchers (esq_kernels.hip); all return hipError_t of the launch
 hipError_t launch_wheel_build(uint64_t* wheel, uint64_t* wheel2, uint32_t shift, hipStream_t s);
 hipError_t launch_col_build(uint32_t* tab, hipStream_t s);
-hipError_t launch_prepare(const Launch& L, Acc* accs, const Interval* iv_single,
-                          uint32_t nseg_total, hipStream_t s);
-hipError_t launch_bucket(const Launch& L, uint32_t n_heavy, uint32_t max_direct, uint32_t max_cof,
+hipError_t launch_prepare(const Launch& L, Acc* accs, uint32_t nseg_total, hipStream_t s);
+hipError_t launch_bucket(const Launch& L, Acc* accs, uint32_t n_heavy, uint32_t max_direct, uint32_t max_cof,
                          uint32_t p_cof, bool in_doubles, const uint4* ranges, uint32_t n_ranges, hipStream_t s);
 hipError_t launch_verify(const Launch& L, uint32_t grid, uint32_t block, hipStream_t s);
 hipError_t launch_tail(const Launch& L, hipStream_t s);

@@ -131,13 +131,25 @@ __device__ __forceinline__ uint32_t bcnt_acc(uint32_t x, uint32_t acc)
 
 // --------------------------------------------------------------- prepare
 
-__global__ void k_prepare(Launch L, Acc* accs, Interval iv0, int write_iv0, uint32_t nseg_total)
+typedef const __attribute__((address_space(4))) Launch CLaunch;
+typedef const __attribute__((address_space(4))) Interval CInterval;
+
+// The kernel's Launch argument (the first of each kernel) and an interval's
+// descriptor as constant memory, for scalar loads: one interval's lies among
+// the arguments themselves, a load that is in flight from the start.
+__device__ __forceinline__ CLaunch* launch_args() { return (CLaunch*)__builtin_amdgcn_kernarg_segment_ptr(); }
+__device__ __forceinline__ CInterval* interval_at(const Interval* iv, uint32_t n_iv, uint32_t ivi)
 {
-    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t stride = gridDim.x * blockDim.x;
-    if (write_iv0 && t == 0)
-        *const_cast<Interval*>(L.iv) = iv0;
-    for (uint32_t i = t; i < L.n_iv * 65u; i += stride) {
+    return n_iv == 1 ? &launch_args()->iv0 : (CInterval*)(uintptr_t)(iv + ivi);
+}
+
+// What a launch needs cleared, by thread t of n: the accumulators, the queue
+// and the list's length; for one interval its descriptor's copy in memory.
+__device__ __forceinline__ void prepare(const Launch& L, Acc* accs, uint32_t t, uint32_t n)
+{
+    if (L.n_iv == 1 && t == 0)
+        *const_cast<Interval*>(L.iv) = L.iv0;
+    for (uint32_t i = t; i < L.n_iv * 65u; i += n) {
         Acc* a = accs + i / 65u;
         const uint32_t k = i % 65u;
         if (k < 16)
@@ -149,24 +161,28 @@ __global__ void k_prepare(Launch L, Acc* accs, Interval iv0, int write_iv0, uint
             a->pad = 0;
         }
     }
-    if (L.bucket_cnt)
-        for (uint32_t i = t; i < nseg_total; i += stride)
-            L.bucket_cnt[i] = 0;
     if (t == 0) {
         *L.queue = 0;
         *L.tail_count = 0;
     }
 }
 
-hipError_t launch_prepare(const Launch& L, Acc* accs, const Interval* iv_single,
-                          uint32_t nseg_total, hipStream_t s)
+__global__ void k_prepare(Launch L, Acc* accs, uint32_t nseg_total)
 {
-    Interval iv0;
-    __builtin_memset(&iv0, 0, sizeof(iv0));
-    if (iv_single)
-        iv0 = *iv_single;
-    hipLaunchKernelGGL(k_prepare, dim3(256), dim3(256), 0, s, L, accs, iv0, iv_single ? 1 : 0,
-                       nseg_total);
+    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t stride = gridDim.x * blockDim.x;
+    prepare(L, accs, t, stride);
+    if (L.bucket_cnt)
+        for (uint32_t i = t; i < nseg_total; i += stride)
+            L.bucket_cnt[i] = 0;
+}
+
+hipError_t launch_prepare(const Launch& L, Acc* accs, uint32_t nseg_total, hipStream_t s)
+{
+    // a thread per counter or accumulator level, at most 256 workgroups
+    const uint64_t work = L.n_iv * 65ull > nseg_total ? L.n_iv * 65ull : nseg_total;
+    const uint32_t grid = work >= 65536 ? 256u : (uint32_t)(work / 256) + 1;
+    hipLaunchKernelGGL(k_prepare, dim3(grid), dim3(256), 0, s, L, accs, nseg_total);
     return hipGetLastError();
 }
 
@@ -322,8 +338,6 @@ __device__ __forceinline__ void cofactor_hits(const Launch& L, uint64_t j, doubl
             hit((j * p * p - 1) / 2 - (uint64_t)B0);
 }
 
-typedef const __attribute__((address_space(4))) Interval CInterval;
-
 // Few segments: grid.y = interval.  Work units, in order: kHeavyLanes-wide
 // groups of lanes for each of the first n_heavy bucket primes (many hits: the
 // group strides over them), then one thread per remaining prime of the direct
@@ -336,7 +350,7 @@ constexpr uint32_t kCofactorLanes = 8;
 __global__ __launch_bounds__(256) void k_bucket(Launch L, uint32_t n_heavy, uint32_t max_direct, uint32_t p_cof,
                                                 int in_doubles)
 {
-    CInterval* iv = (CInterval*)(uintptr_t)(L.iv + blockIdx.y);
+    CInterval* iv = interval_at(L.iv, L.n_iv, blockIdx.y);
     const uint64_t t = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const uint64_t heavy_units = (uint64_t)n_heavy * kHeavyLanes;
     if (iv->nseg == 0)
@@ -374,15 +388,16 @@ __global__ __launch_bounds__(256) void k_bucket(Launch L, uint32_t n_heavy, uint
 
 // Many segments: a workgroup owns up to kOwnSegs consecutive segments of one
 // interval, takes every bucket prime and every cofactor over them, and counts
-// their hits in LDS, so no counter is shared between workgroups (nor cleared
-// beforehand).  Counters in memory bound the other form here: the dies' atomic
+// their hits in LDS, so no counter is shared between workgroups, nor cleared
+// beforehand: the launch's other clearing is done here too and k_prepare left
+// out.  Counters in memory bound the other form here: the dies' atomic
 // operations on them pass the L2 caches, about ten in a nanosecond.  What is
 // left to bound it is finding out that a prime or cofactor has no hit in the
 // range, about a dozen double-precision operations each, 3e4 of them per
 // workgroup near 2^50.  1024 intervals of 2^16 .. 2^28 odd n: 156 us with
 // 64-bit integer reductions, exact square roots for all and counters in memory,
 // 110 with the arithmetic in doubles, 57 here; 2^33 odd n: 20 and 16 us.
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void k_bucket_own(Launch L, const uint4* ranges, uint32_t p_cof, int in_doubles)
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void k_bucket_own(Launch L, Acc* accs, const uint4* ranges, uint32_t p_cof, int in_doubles)
 {
     __shared__ uint32_t s_cnt[kOwnSegs];
     // The cofactors with an integer in their range and the primes with a hit,
@@ -399,11 +414,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
         s0 = rfl(r.y);
         n = rfl(r.z);
     } else {
-        const uint64_t ns = L.iv[0].nseg;
+        const uint64_t ns = L.iv0.nseg;
         s0 = (uint32_t)(blockIdx.x * ns / gridDim.x);
         n = (uint32_t)((blockIdx.x + 1) * ns / gridDim.x) - s0;
     }
-    CInterval* iv = (CInterval*)(uintptr_t)(L.iv + ivi);
+    CInterval* iv = interval_at(L.iv, L.n_iv, ivi);
+    prepare(L, accs, blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x)
         s_cnt[i] = 0;
     if (threadIdx.x == 0)
@@ -497,11 +513,11 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
         L.bucket_cnt[gs + i] = s_cnt[i];
 }
 
-hipError_t launch_bucket(const Launch& L, uint32_t n_heavy, uint32_t max_direct, uint32_t max_cof, uint32_t p_cof,
+hipError_t launch_bucket(const Launch& L, Acc* accs, uint32_t n_heavy, uint32_t max_direct, uint32_t max_cof, uint32_t p_cof,
                          bool in_doubles, const uint4* ranges, uint32_t n_ranges, hipStream_t s)
 {
     if (n_ranges) {
-        hipLaunchKernelGGL(k_bucket_own, dim3(n_ranges), dim3(1024), 0, s, L, ranges, p_cof, in_doubles ? 1 : 0);
+        hipLaunchKernelGGL(k_bucket_own, dim3(n_ranges), dim3(1024), 0, s, L, accs, ranges, p_cof, in_doubles ? 1 : 0);
         return hipGetLastError();
     }
     const uint64_t threads = (uint64_t)n_heavy * kHeavyLanes + max_direct + (uint64_t)max_cof;
@@ -859,9 +875,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
             __syncthreads();
         }
         acc_segs += nsegs;
-        // (scalar loads, from the kernel's arguments for one interval)
-        CInterval& IV = *(L.items ? (CInterval*)(uintptr_t)(L.iv + ivi)
-                                  : &((const __attribute__((address_space(4))) Launch*)__builtin_amdgcn_kernarg_segment_ptr())->iv0);
+        CInterval& IV = *interval_at(L.iv, L.n_iv, ivi);
         const uint32_t cap = L.bucket_cap;
         // The issue arbiter favours older waves, so of the workgroups sharing
         // a CU the first-launched would finish far ahead of the last.  Raising
@@ -1494,8 +1508,7 @@ __global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(8))) 
     // loads) where they are used, through pointers that the compiler takes to
     // change from segment to segment: kept in registers they do not fit, and
     // spilled scalars cost a vector instruction each.
-    typedef const __attribute__((address_space(4))) Launch CLaunch;
-    CLaunch* lp = (CLaunch*)__builtin_amdgcn_kernarg_segment_ptr();
+    CLaunch* lp = launch_args();
     (void)Larg;
 
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = rfl(tid >> 6);
@@ -2102,7 +2115,7 @@ __global__ __launch_bounds__(1024) void k_finalize(Launch L, const Acc* accs, vo
     __shared__ int s_hit;
     __shared__ unsigned long long s_first[66], s_h[65], s_cnt[16];
     const uint32_t ivi = blockIdx.x;
-    CInterval* IV = (CInterval*)(uintptr_t)(L.iv + ivi);
+    CInterval* IV = interval_at(L.iv, L.n_iv, ivi);
     const Acc* A = accs + ivi;
     const uint32_t tid = threadIdx.x, T = blockDim.x;
     const unsigned long long tail_total = *L.tail_count;
