@@ -485,17 +485,18 @@ Geometry geometry(const Params& par, int mode, uint32_t klds, int log2S)
 // Segment length of a launch over n numbers in n_iv intervals: the knob's, or,
 // where that is the default and leaves most of the chip idle, the longest that
 // still makes this many segments (one interval: 128, the sieve alone 64;
-// several: 512), down to 2^14.  2^21 odd n per-n: 18.7 us in 8 segments of
-// 2^18, 14.6 in 128; 2^20 odd m sieved: 9.7 us in one segment, 6 in 64; past
-// these counts shorter segments gain nothing (their halo, tables and starts
-// grow).
+// several: 256), down to 2^14.  2^21 odd n per-n: 18.7 us in 8 segments of
+// 2^18, 12.3 in 128; 2^20 odd m sieved: 9.7 us in one segment, 6.8 in 64; 24
+// intervals of 2^12 .. 2^24 odd n per-n: 24 us at 2^18, 20 at 256 segments, 30
+// at 512.  Past these counts the segments' halo, tables and starts cost more
+// than the idle part of the chip.
 int seg_log2_for(const Params& par, int mode, uint32_t klds, uint64_t n, uint32_t n_iv)
 {
     const Params dflt;
     const int knob = mode == 2 ? par.sieve_seg_log2 : par.seg_log2;
     if (knob != (mode == 2 ? dflt.sieve_seg_log2 : dflt.seg_log2) || column_layout(par, mode, klds))
         return knob;
-    const uint64_t wanted = n_iv > 1 ? 512 : mode == 2 ? 64 : 128;
+    const uint64_t wanted = n_iv > 1 ? 256 : mode == 2 ? 64 : 128;
     int s = knob;
     while (s > kShortSegLog2 && (n >> s) < wanted)
         s--;
@@ -505,12 +506,16 @@ int seg_log2_for(const Params& par, int mode, uint32_t klds, uint64_t n, uint32_
 // Threads per workgroup of the segment kernel in a mode (0 summary, 1 per-n,
 // 2 sieve alone) for a launch of n_iv intervals: per-n batches of many (short)
 // intervals keep the summary block size, which keeps more workgroups resident;
-// segments too short for it take no more than 512.
-uint32_t block_for(const Params& par, int mode, uint32_t n_iv, int log2S)
+// segments too short for it take no more than 512, and so do per-n calls below
+// 2^30 odd n, which are not bound by their stores yet (2^27: 37.4 us with 1024
+// threads, 35.6 with 512; 2^29: 113 and 110; 2^31: 387 and 402).
+uint32_t block_for(const Params& par, int mode, uint32_t n_iv, int log2S, uint64_t n)
 {
     const int b = mode == 2 ? par.sieve_block : mode == 1 && n_iv == 1 ? par.per_n_block : par.block;
     const int knob = mode == 2 ? par.sieve_seg_log2 : par.seg_log2;
-    return (uint32_t)(log2S < knob && log2S <= (mode == 2 ? 17 : 16) ? std::min(b, 512) : b);
+    const bool few = (log2S < knob && log2S <= (mode == 2 ? 17 : 16)) ||
+                     (mode == 1 && n < (1ull << 30) && par.per_n_block == Params().per_n_block);
+    return (uint32_t)(few ? std::min(b, 512) : b);
 }
 
 // The medium-prime tables of the verify geometries for the current knobs
@@ -528,10 +533,12 @@ int prebuild_med_table(Ctx* c, const Params& par)
         const uint32_t klds = v == 2 ? 1u : (uint32_t)par.kh;
         for (int s = seg_log2_for(par, mode, klds, 0, 1); s <= par.seg_log2; s++) {
             const Geometry g = geometry(par, mode, klds, s);
-            const int rc = get_med_table_locked(c, g.rw, g.S, g.col, med_end, (uint32_t)par.entry_hits,
-                                                block_for(par, mode, 1, s), &mt);
-            if (rc)
-                return rc;
+            for (int large = 0; large < 2; large++) {  // block sizes of short and long launches
+                const int rc = get_med_table_locked(c, g.rw, g.S, g.col, med_end, (uint32_t)par.entry_hits,
+                                                    block_for(par, mode, 1, s, large ? ~0ull : 0), &mt);
+                if (rc)
+                    return rc;
+            }
         }
     }
     return ESQ_OK;
@@ -581,7 +588,7 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
         n_all += r.I1 > r.I0 ? r.I1 - r.I0 : 0;
     const int log2S = seg_log2_for(par, mode, klds, n_all, n_iv);
     const Geometry geo = geometry(par, mode, klds, log2S);
-    const uint32_t blk = block_for(par, mode, n_iv, log2S);
+    const uint32_t blk = block_for(par, mode, n_iv, log2S, n_all);
     const uint64_t S = geo.S;
     const uint32_t SW = (uint32_t)(S / 64);
     const uint32_t hlo = geo.hlo, hup = geo.hup, rw = geo.rw;
