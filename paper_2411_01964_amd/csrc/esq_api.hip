@@ -483,18 +483,20 @@ Geometry geometry(const Params& par, int mode, uint32_t klds, int log2S)
 }
 
 // Segment length of a launch over n numbers in n_iv intervals: the knob's, or,
-// where that is the default and leaves most of the chip idle, the longest that
-// still makes this many segments (one interval: 128, the sieve alone 64;
-// several: 256), down to 2^14.  2^21 odd n per-n: 18.7 us in 8 segments of
-// 2^18, 12.3 in 128; 2^20 odd m sieved: 9.7 us in one segment, 6.8 in 64; 24
-// intervals of 2^12 .. 2^24 odd n per-n: 24 us at 2^18, 20 at 256 segments, 30
-// at 512.  Past these counts the segments' halo, tables and starts cost more
-// than the idle part of the chip.
+// where that is the default (and the tail list no longer than its default, so
+// that the few more hit slots meet no scratch limit) and leaves most of the
+// chip idle, the longest that still makes this many segments (one interval:
+// 128, the sieve alone 64; several: 256), down to 2^14.  2^21 odd n per-n: 18.7
+// us in 8 segments of 2^18, 12.3 in 128; 2^20 odd m sieved: 9.7 us in one
+// segment, 6.8 in 64; 24 intervals of 2^12 .. 2^24 odd n per-n: 24 us at 2^18,
+// 20 at 256 segments, 30 at 512.  Past these counts the segments' halo, tables
+// and starts cost more than the idle part of the chip.
 int seg_log2_for(const Params& par, int mode, uint32_t klds, uint64_t n, uint32_t n_iv)
 {
     const Params dflt;
     const int knob = mode == 2 ? par.sieve_seg_log2 : par.seg_log2;
-    if (knob != (mode == 2 ? dflt.sieve_seg_log2 : dflt.seg_log2) || column_layout(par, mode, klds))
+    if (knob != (mode == 2 ? dflt.sieve_seg_log2 : dflt.seg_log2) || par.tail_cap > dflt.tail_cap ||
+        column_layout(par, mode, klds))
         return knob;
     const uint64_t wanted = n_iv > 1 ? 256 : mode == 2 ? 64 : 128;
     int s = knob;
@@ -576,6 +578,15 @@ struct Planned {
     size_t o_tn = 0, o_tiv = 0, o_td = 0;
 };
 
+// Hit slots per segment (4 bytes each, and 4 for the segment's count) when n
+// segments and `extra` words more take no more than n_row segments of cap_row
+// slots; at least one.
+uint32_t slots_per_segment(uint64_t n_row, uint32_t cap_row, uint64_t n, uint64_t extra)
+{
+    const uint64_t words = n_row * ((uint64_t)cap_row + 1);
+    return words > extra + 2 * n ? (uint32_t)((words - extra) / n - 1) : 1u;
+}
+
 // Plan one launch over `reqs` (mode 0/1 verify, 2 sieve).
 int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<Req>& reqs,
          bool exc_list, Planned* P, bool no_alloc = false)
@@ -598,7 +609,7 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     // per-interval geometry
     std::vector<Interval>& ivs = P->ivs;
     ivs.assign(n_iv, Interval());
-    uint64_t nseg_total = 0, pmax_all = 0;
+    uint64_t nseg_total = 0, nseg_row = 0, pmax_all = 0;  // nseg_row: the row layout's segments
     std::vector<uint64_t> pmax(n_iv, 0);
     for (uint32_t i = 0; i < n_iv; i++) {
         const Req& r = reqs[i];
@@ -619,6 +630,8 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
             pmax[i] = isqrt_u64(2 * (r.I1 - 1) + 1);                // last odd m
         } else {
             nseg = (r.I1 - (uint64_t)v.A0 + S - 1) / S;
+            if (col)
+                nseg_row += (r.I1 - (r.I0 & ~63ull) + (1u << kColLog2) - 1) >> kColLog2;
             const uint64_t n_last = 2 * (r.I1 - 1) + 1;
             pmax[i] = n_last >= 3 ? isqrt_u64(n_last - 2) : 0;       // largest candidate
         }
@@ -763,13 +776,19 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
 
     uint32_t cap = 0;
     if (any_bucket) {
-        if (par.bucket_cap > 0) {
-            cap = (uint32_t)par.bucket_cap;
-        } else {
-            const double expect = (double)R * (c->inv_pref[pmax_end_all] - c->inv_pref[med_end]);
-            cap = (uint32_t)std::ceil(8.0 * expect + 32.0);
-            cap = (cap + 7) & ~7u;
-        }
+        const double density = c->inv_pref[pmax_end_all] - c->inv_pref[med_end];
+        auto slots = [&](uint64_t region) {
+            const uint32_t n = (uint32_t)std::ceil(8.0 * (double)region * density + 32.0);
+            return par.bucket_cap > 0 ? (uint32_t)par.bucket_cap : (n + 7) & ~7u;
+        };
+        // The column layout has 1.6% more segments (its region holds the halo
+        // too): they share the row layout's slots, so that no call needs more
+        // scratch than that layout would and a limit on it (the static array
+        // of esq_verify_range_noalloc, a server's budget) admits the same calls
+        // (64 words for the alignment between the two, in calls of that size).
+        cap = col ? slots_per_segment(nseg_row, slots((1u << kColLog2) + kColHalo), nseg_total,
+                                      4 * P->ranges.size() + (nseg_total >= 1024 ? 64 : 0))
+                  : slots(R);
     }
 
     // LDS of the segment kernel: bitmap + medium-prime tables (+ tasks if they fit)

@@ -10,6 +10,7 @@ import torch
 import oracle
 from paper_2411_01964_amd import esq
 from tests.test_gpu_parity import DEFAULTS, MAX_HI, assert_same, knobs
+from tests.test_zz_no_alloc import KEYS, noalloc_call
 
 pytestmark = pytest.mark.gpu
 
@@ -82,3 +83,20 @@ def test_batch_of_column_intervals():
     for (a, b), g in zip(ivs, got):
         w = esq.verify_range(a, b)
         assert all(g[k] == w[k] for k in g)
+
+
+def test_a_scratch_limit_admits_what_the_row_layout_needs():
+    """The longest interval below 2^50 whose scratch in the row layout fits the
+    static array: the column layout takes it too."""
+    hi, limit = 1 << 50, esq.ESQ_NOALLOC_SCRATCH_MAX
+    knobs(block=256)
+    a, b = 1 << 33, 1 << 37
+    while b - a > 1:
+        mid = (a + b) // 2
+        a, b = (mid, b) if esq.scratch_bytes([hi - 2 * mid + 1], [hi]) <= limit else (a, mid)
+    lo = hi - 2 * a + 1
+    row = esq.verify_range(lo, hi)
+    knobs()
+    assert esq.scratch_bytes([lo], [hi]) <= limit
+    got = noalloc_call(lo, hi)
+    assert all(got[k] == row[k] for k in KEYS)
