@@ -50,10 +50,11 @@ LDS_BYTES_PER_N = 0.125 + 4 * 0.02241 + 0.125
 #  large primes' 1.23e-4 hits per n): 0.125 + 4 * (0.02234 + 0.000123) B/n.
 SIEVE_LDS_BYTES_PER_N = 0.125 + 4 * (0.02234 + 0.000123)
 MARKS_PER_N = 0.02234 + 0.000123     # medium (17 <= p <= 4093) and large primes
-#  VALU lane-ops: 6 per search step per 64-n word (two funnel shifts, two ANDs,
-#  two popcounts) times the expected number of steps per word, 2.928, from the
-#  probabilities of Table 2 (1 + sum_k P(some of 64 n unresolved after k)).
-VALU_OPS_PER_N = 6 * 2.928 / 64
+#  VALU lane-ops: 4 per search step per 64-n word (two ANDs, two popcounts: in
+#  the column layout the windows need no shift) times the expected number of
+#  steps per word, 2.928, from the probabilities of Table 2 (1 + sum_k P(some of
+#  64 n unresolved after k)).
+VALU_OPS_PER_N = 4 * 2.928 / 64
 
 CONFIG_NAMES = ("odd_below_2pow22", "odd_2pow31_at_2pow40", "odd_2pow33_below_2pow50",
                 "batch_4096_intervals", "served_poisson_2000")
@@ -232,14 +233,15 @@ def run_range(lo, hi, steps, warmup, streams, per_n=False, prof_steps=20):
 
 
 def sieve_phase(n, kernel_s, ph, ceil, traffic):
-    """The segment kernel's time split by the phase clock, each phase against
-    the ceiling that binds it: init (16-byte L2 reads of the two pattern
-    tables, 16 bytes per region word) against the L2 read ceiling, marking
-    (one ds_or_b32 per odd multiple of p^2, p >= 17) against the ds_or_b32
-    ceiling, search (the algorithmic VALU operations, a third of them full
-    rate, two thirds funnel shifts and popcounts) against the measured mix of
-    those rates.  The sieve phase (init + marking) carries the paper's LDS
-    traffic against the measured LDS peak."""
+    """The segment kernel's time split by the phase clock, and each phase's work
+    over the kernel's whole time (the phases of the workgroups that share a CU
+    overlap, so a phase's own time bounds no rate) against the ceiling of its
+    unit: init (16-byte L2 reads of the two pattern tables, 16 bytes per 64
+    region positions) against the L2 read ceiling, marking (one ds_or_b32 per
+    odd multiple of p^2, p >= 17) against the ds_or_b32 ceiling, search (the
+    algorithmic VALU operations, half ANDs, half popcounts) against the measured
+    mix of those rates.  The sieve phase (init + marking) carries the paper's
+    LDS traffic against the measured LDS peak."""
     from paper_2411_01964_amd import esq
 
     tot = max(1, sum(ph.values()))
@@ -256,8 +258,7 @@ def sieve_phase(n, kernel_s, ph, ceil, traffic):
     region = rw_words * 64
     l2_bytes = n / S * rw_words * 16
     marks = n * region / S * MARKS_PER_N
-    mix = 1.0 / ((1 / ceil["valu_int32_ops_per_s"] + 1 / ceil["valu_alignbit_ops_per_s"] +
-                  1 / ceil["valu_bcnt_ops_per_s"]) / 3)
+    mix = 2.0 / (1 / ceil["valu_int32_ops_per_s"] + 1 / ceil["valu_bcnt_ops_per_s"])
     lds_meas = max(ceil["lds_write_b64_Bps"], ceil["lds_read_b64_Bps"])
     sieve_s = t_init + t_mark
     out = {
@@ -269,17 +270,17 @@ def sieve_phase(n, kernel_s, ph, ceil, traffic):
         "frac_measured": SIEVE_LDS_BYTES_PER_N * n / sieve_s / lds_meas,
         "frac_nominal": SIEVE_LDS_BYTES_PER_N * n / sieve_s / LDS_PEAK,
         "init": {"ms": t_init * 1e3, "bound": "l2 read", "l2_bytes": l2_bytes,
-                 "achieved_GBps": l2_bytes / t_init / 1e9,
+                 "achieved_GBps": l2_bytes / kernel_s / 1e9,
                  "ceiling_GBps": ceil["l2_read_Bps"] / 1e9,
-                 "frac_of_ceiling": l2_bytes / t_init / ceil["l2_read_Bps"]},
+                 "frac_of_ceiling": l2_bytes / kernel_s / ceil["l2_read_Bps"]},
         "mark": {"ms": t_mark * 1e3, "bound": "ds_or_b32", "marks": marks,
-                 "achieved_GBps": 4 * marks / t_mark / 1e9,
+                 "achieved_GBps": 4 * marks / kernel_s / 1e9,
                  "ceiling_GBps": ceil["lds_or_b32_Bps"] / 1e9,
-                 "frac_of_ceiling": 4 * marks / t_mark / ceil["lds_or_b32_Bps"]},
+                 "frac_of_ceiling": 4 * marks / kernel_s / ceil["lds_or_b32_Bps"]},
         "search": {"ms": t_search * 1e3, "bound": "valu mix",
-                   "achieved_Tops": VALU_OPS_PER_N * n / t_search / 1e12,
+                   "achieved_Tops": VALU_OPS_PER_N * n / kernel_s / 1e12,
                    "ceiling_Tops": mix / 1e12,
-                   "frac_of_ceiling": VALU_OPS_PER_N * n / t_search / mix},
+                   "frac_of_ceiling": VALU_OPS_PER_N * n / kernel_s / mix},
     }
     if traffic and traffic.get("valu_lane_ops") is not None:
         out["issued_valu_Tops"] = traffic["valu_lane_ops"] / kernel_s / 1e12

@@ -3,7 +3,8 @@
 // operations over 64-bit words.
 //
 //   k_wheel_build  periodic patterns of odd multiples of 9, 25, 49 and of 121, 169 (once)
-//   k_prepare      zero the per-launch accumulators and the work queue
+//   k_prepare      zero the per-launch accumulators, hit counts and work queue
+//                  (k_bucket_own does this itself)
 //   k_bucket       primes above the medium range: every odd multiple of p^2
 //                  that falls in a segment region goes to that segment's hit
 //                  slots (by first hit up to a cut-over chosen per launch, at
@@ -17,8 +18,10 @@
 //                  bit-sliced scan of the LDS bitmap (in per-n mode also one
 //                  byte per n to HBM, staged through LDS; in sieve mode the
 //                  bitmap itself to HBM)
-//   k_tail         exact search for the rare n not resolved from LDS
-//   k_finalize     per interval: aggregates, record-setters, exceptions
+//   k_tail         exact search for the n not resolved from LDS: a launch of its
+//                  own only where they may be many (depths below 12 in LDS)
+//   k_finalize     per interval: the tail search where it has no launch of its
+//                  own; aggregates, record-setters, exceptions
 #include <type_traits>
 
 #include "esq.h"
@@ -1484,8 +1487,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
 // bits by workgroups of kColBlock threads, four of them on a CU.
 //
 // What bounds it: the issue of vector instructions and the waits between them.
-// Per 64-n word the row layout's summary form issues 65 vector instructions
-// (30 in the search, a third of them half-rate funnel shifts) and 45 scalar
+// Per 64-n word the row layout's summary form issues 52 vector instructions
+// (30 in the search, a third of them half-rate funnel shifts) and 31 scalar
 // ones; here it is 42 and 17, of which the search has 23 (8 popcounts, 8
 // ANDs).  The vector units are busy for about 0.6 of the time, the LDS for
 // 0.47; the rest are barriers and latencies of eight waves a SIMD, which is
