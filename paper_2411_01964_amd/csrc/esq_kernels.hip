@@ -1624,7 +1624,14 @@ __global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(8))) 
 #pragma unroll
             for (int k = 0; k <= kRegLevels; k++)
                 cnt[k] = 0;
-            found = 0;
+            // Segment 0 holds the interval's least n of depths 2 .. 5, so runs
+            // that start later need not look for theirs: the n whose first
+            // four candidates are multiples of 9, 25, 49 and 121 in any order
+            // recur within 169400 odd numbers (a period of 9 25 49 121).  Every
+            // run's first segment took the slow form for these offers: 2^31
+            // odd n 66 us with it, 56 without.
+            static_assert(S >= 169400, "a whole segment holds an n of depth 5 or more");
+            found = seg0 ? 0x3cu : 0u;
             acc_segs = 0;
             cur_iv = ivi;
             __syncthreads();
@@ -1842,7 +1849,7 @@ __global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(8))) 
             // Four words per lane.  KIND 0: every slot of the wave's 256 words
             // is an n of the segment; 1: all but those in bit 0 (words below 0
             // from the guard); 2: the general form, which also wraps below
-            // word 0 and offers levels 5 and 6.
+            // word 0 and offers level 5.
             auto quad_pass = [&](auto kind_c, uint32_t i0) {
                 constexpr int KIND = decltype(kind_c)::value;
                 auto quad = [&](int32_t i) {
@@ -1891,7 +1898,7 @@ __global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(8))) 
 #pragma unroll
                 for (int c = 0; c < 4; c++)
                     cnt[5] = bcnt_acc(u[c], cnt[5]);
-                if (KIND == 2 && !(found & (1u << 6)))
+                if (!(found & (1u << 6)))
                     offer(6, i0, u);
                 const uint32_t klds = lp->k_lds;
                 uint32_t k = 5;
@@ -1943,8 +1950,8 @@ __global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(8))) 
             // opaque, so that no addresses are kept from segment to segment
             uint32_t t4 = 4 * tid;
             asm volatile("" : "+v"(t4));
-            if (yhi == R && (found & 0x60u) == 0x60u) {
-                // a whole segment, the levels up to 6 offered
+            if (yhi == R && (found & (1u << 5))) {
+                // a whole segment, the levels up to 5 offered
                 if (wave == 0 && lane < kColGuard)  // only this wave reads the guard
                     bm[(int32_t)lane - (int32_t)kColGuard] = bm[W - kColGuard + lane] << 1;
 #pragma unroll
@@ -1964,7 +1971,7 @@ __global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(8))) 
             __syncthreads();
             // the levels found by now need no offers in later segments
             if ((found & 0x7cu) != 0x7cu) {
-                uint32_t fnd = 0;
+                uint32_t fnd = found;
 #pragma unroll
                 for (int k = 2; k <= 6; k++)
                     fnd |= s_first[k] != kNone ? 1u << k : 0u;

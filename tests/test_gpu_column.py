@@ -9,6 +9,7 @@ import torch
 
 import oracle
 from paper_2411_01964_amd import esq
+from tests.test_depth_gap import longest_gap
 from tests.test_gpu_parity import DEFAULTS, MAX_HI, assert_same, knobs
 from tests.test_zz_no_alloc import KEYS, noalloc_call
 
@@ -100,3 +101,14 @@ def test_a_scratch_limit_admits_what_the_row_layout_needs():
     assert esq.scratch_bytes([lo], [hi]) <= limit
     got = noalloc_call(lo, hi)
     assert all(got[k] == row[k] for k in KEYS)
+
+
+@pytest.mark.parametrize("base", [0, 1 << 40, (1 << 50) - (1 << 23)])
+def test_least_n_of_each_depth_after_the_longest_gap(base):
+    """Intervals that start where the n of depth 5 and more are furthest away
+    (for 9, 25, 49 and 121 alone): the records come from the first segment."""
+    gap, at = longest_gap()
+    period = 9 * 25 * 49 * 121
+    first = base // 2 + (at - base // 2) % period + 1
+    for i in (first, first + gap - SEG):
+        same_as_per_n(2 * i + 1, 2 * i + 1 + 2 * 3 * SEG)
