@@ -774,6 +774,10 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
         }
     }
 
+    // copies of one interval's accumulators (see Acc): where a caller's knobs
+    // set the scratch's size there is one, as there is no room to take
+    const uint32_t n_acc = n_iv == 1 && mode != 2 && par.bucket_cap == 0 && par.tail_cap <= Params().tail_cap
+                               ? kAccCopies : n_iv;
     uint32_t cap = 0;
     if (any_bucket) {
         const double density = c->inv_pref[pmax_end_all] - c->inv_pref[med_end];
@@ -786,9 +790,17 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
         // scratch than that layout would and a limit on it (the static array
         // of esq_verify_range_noalloc, a server's budget) admits the same calls
         // (64 words for the alignment between the two, in calls of that size).
-        cap = col ? slots_per_segment(nseg_row, slots((1u << kColLog2) + kColHalo), nseg_total,
-                                      4 * P->ranges.size() + (nseg_total >= 1024 ? 64 : 0))
-                  : slots(R);
+        // The copies of the accumulators come out of the slots likewise.
+        const bool large = nseg_total >= 1024;
+        const uint64_t copies = large ? 64 + (n_acc - n_iv) * sizeof(Acc) / 4 : 0;
+        auto less_copies = [&](uint64_t n, uint32_t slots_row) {
+            return n_acc > n_iv ? slots_per_segment(n, slots_row, n, copies) : slots_row;
+        };
+        if (col)
+            cap = slots_per_segment(nseg_row, less_copies(nseg_row, slots((1u << kColLog2) + kColHalo)),
+                                    nseg_total, 4 * P->ranges.size() + (large ? 64 : 0));
+        else
+            cap = less_copies(nseg_total, slots(R));
     }
 
     // LDS of the segment kernel: bitmap + medium-prime tables (+ tasks if they fit)
@@ -871,7 +883,7 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     P->o_ranges = off;
     off = align_up(off + sizeof(uint4) * P->ranges.size());
     P->o_acc = off;
-    off = align_up(off + sizeof(Acc) * std::max<uint32_t>(n_iv, 1));
+    off = align_up(off + sizeof(Acc) * std::max<uint32_t>(n_acc, 1));
     P->o_bcnt = off;
     off = align_up(off + (any_bucket ? nseg_total * 4 : 0));
     P->o_bslot = off;
@@ -894,6 +906,7 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     L.hup_words = hup;
     L.rw = rw;
     L.n_iv = n_iv;
+    L.n_acc = n_acc;
     L.n_items = n_items;
     L.run_long = run_long;
     L.run_short = run_short;

@@ -54,10 +54,15 @@ constexpr uint32_t kFlushSegs = 4096;     // segments per run and per flush of p
 constexpr int kMinSegLog2 = 10;
 constexpr int kShortSegLog2 = 14;         // shortest segment of a short launch at the default knobs
 constexpr uint32_t kFinalizeSortCap = 16384;  // LDS sort capacity of the finalize pass
+constexpr uint32_t kAccCopies = 16;       // of one interval's accumulators (a power of two)
 constexpr uint32_t kOwnSegs = 256;        // segments per workgroup of k_bucket_own, at most
 constexpr uint64_t kCofactorPrime = 1u << 20; // largest direct/cofactor cut-over considered
 
-// Per-interval accumulators in device scratch.
+// Per-interval accumulators in device scratch.  A launch of one interval has
+// kAccCopies of them: workgroup b adds its counts and least n to copy b mod
+// that, and k_finalize merges them.  Device-scope operations on one address take
+// about 12 ns each, one after the other: a thousand workgroups that end
+// together waited 12 us for each other's.
 struct Acc {
     unsigned long long cnt[16];        // cnt[k]: #n still unresolved after step k (k <= k_lds)
     unsigned long long first[65];      // first[k]: least n-index with depth >= k
@@ -96,6 +101,7 @@ struct Launch {
     uint64_t s_inv;               // floor((2^64 - 1) / S)
     uint32_t hlo_words, hup_words, rw;  // rw = hlo_words + S/64 + hup_words (column layout: R/64)
     uint32_t n_iv;                // intervals
+    uint32_t n_acc;               // accumulators: n_iv, or one interval's copies
     uint32_t n_items;             // work items in the queue
     uint32_t run_long, run_short; // one interval: see run_of
     uint32_t stage;               // per-n mode: depth bytes staged through LDS per wave

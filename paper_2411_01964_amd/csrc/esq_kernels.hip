@@ -152,7 +152,7 @@ __device__ __forceinline__ void prepare(const Launch& L, Acc* accs, uint32_t t, 
 {
     if (L.n_iv == 1 && t == 0)
         *const_cast<Interval*>(L.iv) = L.iv0;
-    for (uint32_t i = t; i < L.n_iv * 65u; i += n) {
+    for (uint32_t i = t; i < L.n_acc * 65u; i += n) {
         Acc* a = accs + i / 65u;
         const uint32_t k = i % 65u;
         if (k < 16)
@@ -183,7 +183,7 @@ __global__ void k_prepare(Launch L, Acc* accs, uint32_t nseg_total)
 hipError_t launch_prepare(const Launch& L, Acc* accs, uint32_t nseg_total, hipStream_t s)
 {
     // a thread per counter or accumulator level, at most 256 workgroups
-    const uint64_t work = L.n_iv * 65ull > nseg_total ? L.n_iv * 65ull : nseg_total;
+    const uint64_t work = L.n_acc * 65ull > nseg_total ? L.n_acc * 65ull : nseg_total;
     const uint32_t grid = work >= 65536 ? 256u : (uint32_t)(work / 256) + 1;
     hipLaunchKernelGGL(k_prepare, dim3(grid), dim3(256), 0, s, L, accs, nseg_total);
     return hipGetLastError();
@@ -778,7 +778,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
     uint32_t acc_segs = 0;    // segments in the partial totals
     auto flush = [&](uint32_t iv) {
         if (MODE != 2) {
-            Acc* acc = L.items ? L.iv[iv].acc : L.iv0.acc;
+            Acc* acc = L.items ? L.iv[iv].acc : L.iv0.acc + (blockIdx.x & (L.n_acc - 1));
 #pragma unroll
             for (int k = 1; k <= kRegLevels; k++) {
                 if (k > (int)klds)
@@ -1549,7 +1549,7 @@ __global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(8))) 
     uint32_t cur_iv = ~0u, acc_segs = 0;
     auto flush = [&](uint32_t iv) {
         asm volatile("" : "+s"(lp));
-        Acc* acc = lp->items ? lp->iv[iv].acc : lp->iv0.acc;
+        Acc* acc = lp->items ? lp->iv[iv].acc : lp->iv0.acc + (blockIdx.x & (lp->n_acc - 1));
         const uint32_t klds = lp->k_lds;
 #pragma unroll
         for (int k = 1; k <= kRegLevels; k++) {
@@ -2136,13 +2136,30 @@ __global__ __launch_bounds__(1024) void k_finalize(Launch L, const Acc* accs, vo
     // still unresolved after step k_lds are the exceptions, and they are
     // deeper than every level, so first[k] for k > k_lds + 1 is first[k_lds + 1]
     const bool no_tail = L.k_lds >= L.kmax_eff;
+    // one interval's copies: a thread per copy and level (256 of them)
+    static_assert(kAccCopies * 16 <= 256 && kMaxKh + 1 < 16, "the copies' levels");
+    const uint32_t copy = tid >> 4, lev = tid & 15u;
+    const bool merge = L.n_iv == 1 && copy > 0 && copy < L.n_acc;
+    const unsigned long long c_cnt = merge ? A[copy].cnt[lev] : 0ull;
+    const unsigned long long c_first = merge ? A[copy].first[lev] : kNone;
     for (uint32_t i = tid; i < 65; i += T) {
-        s_first[i] = (no_tail && i > L.k_lds + 1) ? A->first[L.k_lds + 1] : A->first[i];
+        s_first[i] = A->first[i];
         s_h[i] = no_tail ? 0ull : A->deep_hist[i];
         if (i < 16)
             s_cnt[i] = A->cnt[i];
     }
     __syncthreads();
+    if (c_cnt)
+        atomicAdd(&s_cnt[lev], c_cnt);
+    if (c_first != kNone)
+        atomicMin(&s_first[lev], c_first);
+    __syncthreads();
+    if (no_tail) {
+        for (uint32_t i = tid; i < 65; i += T)
+            if (i > L.k_lds + 1)
+                s_first[i] = s_first[L.k_lds + 1];
+        __syncthreads();
+    }
     if (tail && !no_tail)
         for (uint64_t idx = 0; idx < nlist; idx++) {
             if (L.tail_iv[idx] != ivi)
