@@ -1489,14 +1489,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
 // What bounds it: the issue of vector instructions and the waits between them.
 // Per 64-n word the row layout's summary form issues 52 vector instructions
 // (30 in the search, a third of them half-rate funnel shifts) and 31 scalar
-// ones; here it is 42 and 17, of which the search has 23 (8 popcounts, 8
+// ones; here it is 39 and 18, of which the search has 23 (8 popcounts, 8
 // ANDs).  The vector units are busy for about 0.6 of the time, the LDS for
 // 0.47; the rest are barriers and latencies of eight waves a SIMD, which is
 // why block size, region length and trip counts are constants and the rare
 // paths (first segments, deep n) have loops of their own: with runtime trip
 // counts and the offers in the common path the same method took 204 us.
-// On the 2^33 odd n below 2^50: 221 us in the row layout, 174 us here (4.9e13
-// n/s); a third table for 17 and 19 took 184, regions of 2^19 211, of 2^17
+// On the 2^33 odd n below 2^50: 221 us in the row layout, 160 to 167 us here
+// (5.2e13 n/s); a third table for 17 and 19 took 184, regions of 2^19 211, of 2^17
 // 203.
 template <bool PH>
 __global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_column(Launch Larg)
@@ -2114,6 +2114,105 @@ __device__ unsigned long long block_sum(unsigned long long v, unsigned long long
     return r;
 }
 
+// Sort the `got` distinct numbers in s_sort, by a workgroup of kSortThreads: each
+// goes to the bucket of its leading bits (s_bkt: kSortBuckets + 1 words) and
+// takes its rank among the bucket's, at most eight on average: exceptions lie
+// about evenly over their range, being set by residues (crowded ones would
+// take longer, a pass over the bucket each).  What bounds it is the latency of
+// its steps: k_finalize with 2400 exceptions takes 10.5 us, with a bitonic sort
+// (78 steps for 4096 entries) 31.
+constexpr uint32_t kSortThreads = 1024, kSortBuckets = 4 * kSortThreads;
+constexpr size_t kFinalizeLds = (size_t)kFinalizeSortCap * 8 + (kSortBuckets + 2) * 4;
+__device__ __forceinline__ void bucket_sort(unsigned long long* s_sort, uint32_t* s_bkt, uint32_t got)
+{
+    constexpr int kEach = (int)(kFinalizeSortCap / kSortThreads);
+    __shared__ unsigned long long s_lo, s_hi;
+    __shared__ uint32_t s_wave[kSortThreads / 64];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6;
+    if (tid == 0) {
+        s_lo = kNone;
+        s_hi = 0;
+    }
+    for (uint32_t i = tid; i < kSortBuckets; i += kSortThreads)
+        s_bkt[i] = 0;
+    unsigned long long x[kEach], lo = kNone, hi = 0;
+#pragma unroll
+    for (int u = 0; u < kEach; u++) {
+        const uint32_t i = tid + u * kSortThreads;
+        x[u] = kNone;
+        if (i < got) {
+            x[u] = s_sort[i];
+            lo = min(lo, x[u]);
+            hi = max(hi, x[u]);
+        }
+    }
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = min(lo, (unsigned long long)__shfl_xor(lo, o));
+        hi = max(hi, (unsigned long long)__shfl_xor(hi, o));
+    }
+    __syncthreads();
+    if (lane == 0) {
+        atomicMin(&s_lo, lo);
+        atomicMax(&s_hi, hi);
+    }
+    __syncthreads();
+    lo = s_lo;
+    const int bits = 64 - __clzll((long long)(s_hi - lo));
+    const int shift = bits > 12 ? bits - 12 : 0;
+    static_assert(kSortBuckets == 1u << 12, "the leading bits");
+    uint32_t at[kEach];  // place in the bucket, later in s_sort
+#pragma unroll
+    for (int u = 0; u < kEach; u++)
+        if (tid + u * kSortThreads < got)
+            at[u] = atomicAdd(&s_bkt[(uint32_t)((x[u] - lo) >> shift)], 1u);
+    __syncthreads();
+    // the buckets' starts: four buckets a thread
+    uint32_t n[4], sum = 0;
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        n[j] = s_bkt[4 * tid + j];
+        sum += n[j];
+    }
+    uint32_t up = sum;
+    for (int o = 1; o < 64; o <<= 1) {
+        const uint32_t v = __shfl_up(up, o);
+        up += lane >= (uint32_t)o ? v : 0u;
+    }
+    if (lane == 63)
+        s_wave[wave] = up;
+    __syncthreads();
+    uint32_t start = up - sum;
+    for (uint32_t w = 0; w < wave; w++)
+        start += s_wave[w];
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        s_bkt[4 * tid + j] = start;
+        start += n[j];
+    }
+    if (tid == kSortThreads - 1)
+        s_bkt[kSortBuckets] = start;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kEach; u++)
+        if (tid + u * kSortThreads < got)
+            s_sort[s_bkt[(uint32_t)((x[u] - lo) >> shift)] + at[u]] = x[u];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kEach; u++)
+        if (tid + u * kSortThreads < got) {
+            const uint32_t b = (uint32_t)((x[u] - lo) >> shift), end = s_bkt[b + 1];
+            at[u] = s_bkt[b];
+            for (uint32_t i = s_bkt[b]; i < end; i++)
+                at[u] += s_sort[i] < x[u] ? 1u : 0u;
+        }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kEach; u++)
+        if (tid + u * kSortThreads < got)
+            s_sort[at[u]] = x[u];
+    __syncthreads();
+}
+
 // One workgroup per interval; the aggregates by its first wave, a level per
 // lane (one thread taking the 65 levels in turn took 4 of the kernel's 6 us).
 __global__ __launch_bounds__(1024) void k_finalize(Launch L, const Acc* accs, void* out_summaries, void* out_records,
@@ -2222,46 +2321,7 @@ __global__ __launch_bounds__(1024) void k_finalize(Launch L, const Acc* accs, vo
         }
         __syncthreads();
         const uint32_t got = min(s_fill, kFinalizeSortCap);
-        uint32_t n2 = T;  // a power of two
-        while (n2 < got)
-            n2 <<= 1;
-        for (uint32_t i = got + tid; i < n2; i += T)
-            s_sort[i] = kNone;
-        __syncthreads();
-        // bitonic sort; each wave holds a contiguous stretch, so only the steps
-        // whose partners lie further apart than that need the workgroup's
-        // barrier (10 of 78 for 4096 entries; with one at each, and half the
-        // lanes idle, the kernel took 62 us for 2400 exceptions, now 31)
-        const uint32_t stretch = n2 / (T >> 6), w0 = (tid >> 6) * stretch;
-        bool wide = false;  // the last step crossed stretches
-        for (uint32_t k = 2; k <= n2; k <<= 1)
-            for (uint32_t j = k >> 1; j > 0; j >>= 1) {
-                if (j >= stretch || wide)
-                    __syncthreads();
-                wide = j >= stretch;
-                // a lane per pair (i, i + j), two pairs in flight
-                const uint32_t t1 = (w0 + stretch) / 2;
-                for (uint32_t t = w0 / 2 + (tid & 63u); t < t1; t += 128) {
-                    uint32_t i[2];
-                    unsigned long long x[2], y[2];
-#pragma unroll
-                    for (int u = 0; u < 2; u++) {
-                        const uint32_t tu = t + 64 * u < t1 ? t + 64 * u : t;
-                        i[u] = 2 * tu - (tu & (j - 1));
-                        x[u] = s_sort[i[u]];
-                        y[u] = s_sort[i[u] + j];
-                    }
-#pragma unroll
-                    for (int u = 0; u < 2; u++)
-                        if ((u == 0 || t + 64 < t1) && (x[u] > y[u]) == ((i[u] & k) == 0)) {
-                            s_sort[i[u]] = y[u];
-                            s_sort[i[u] + j] = x[u];
-                        }
-                }
-                __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-            }
-        __syncthreads();
+        bucket_sort(s_sort, (uint32_t*)(s_sort + kFinalizeSortCap), got);
         for (uint32_t i = tid; i < want && i < got; i += T)
             out_exceptions[i] = 2 * s_sort[i] + 1;
     }
@@ -2317,8 +2377,8 @@ hipError_t launch_finalize(const Launch& L, const Acc* accs, void* out_summaries
 {
     if (L.n_iv == 0)
         return hipSuccess;
-    const size_t lds = out_exceptions ? (size_t)kFinalizeSortCap * 8 : 0;
-    hipLaunchKernelGGL(k_finalize, dim3(L.n_iv), dim3(out_exceptions ? 1024 : 256), lds, s, L, accs,
+    const size_t lds = out_exceptions ? kFinalizeLds : 0;
+    hipLaunchKernelGGL(k_finalize, dim3(L.n_iv), dim3(out_exceptions ? kSortThreads : 256), lds, s, L, accs,
                        out_summaries, out_records, out_exceptions, exc_cap, tail_in_finalize(L) ? 1 : 0);
     return hipGetLastError();
 }
@@ -2334,7 +2394,7 @@ hipError_t configure_kernels()
             if (e != hipSuccess) return e;
         }
     e = hipFuncSetAttribute((const void*)k_finalize, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)(kFinalizeSortCap * 8));
+                            (int)kFinalizeLds);
     return e;
 }
 
