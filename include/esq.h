@@ -192,9 +192,9 @@ int esq_verify_batch(uint32_t count, const uint64_t *lo, const uint64_t *hi, uin
  * intervals holds while it runs (a kept block or pool memory): per-segment
  * hit slots of the large primes, the list of n left to the exact tail pass,
  * per-interval descriptors and accumulators.  The caller's outputs
- * (summaries, records, per-n bytes) are not included.  For count = 1 it is
- * also the scratch of esq_verify_range on that interval with
- * exceptions_cap = 0.  For admission control by a server: a request is
+ * (summaries, records, per-n bytes) are not included.  It is the larger of
+ * the figures with and without per-n outputs.  For count = 1 it is also the
+ * scratch of esq_verify_range on that interval with exceptions_cap = 0.  For admission control by a server: a request is
  * admitted when its scratch and its outputs fit in device memory.
  *   count, lo, hi, kmax  as in esq_verify_batch (host arrays)
  *   out_bytes            host, required
@@ -232,16 +232,20 @@ void esq_batch_destroy(esq_batch *batch);
  *   "seg_log2"   log2 of the segment length in odd numbers held in LDS (10..20).
  *                Aggregates-only calls whose search goes past step 4 run a
  *                kernel of their own when seg_log2 is 18, kh 13 and block 512
- *                (the defaults); its segments are 4096 odd numbers shorter
+ *                (the defaults); its segments are 4096 odd numbers shorter.
+ *                At the default 18, per-n calls and searches to step 4 too
+ *                short to fill the device take shorter segments (to 2^14)
  *   "sieve_seg_log2" the same for esq_sieve_segment (default 20: one
  *                workgroup per CU whose storer waves write the bitmap while
- *                its loader waves start the next segment)
+ *                its loader waves start the next segment; at the default,
+ *                short calls take shorter segments)
  *   "kh"         deepest k resolved from the LDS bitmap (1..13); deeper k go
  *                to the exact tail pass
  *   "block"      threads per workgroup of the segment kernel, summary mode
  *                (64..1024, x64; default 512)
- *   "per_n_block" the same in per-n mode for one interval (default 1024;
- *                per-n batches of several intervals use "block")
+ *   "per_n_block" the same in per-n mode for one interval (default 1024, of
+ *                which calls below 2^30 odd n take 512; per-n batches of
+ *                several intervals use "block")
  *   "sieve_block" the same for esq_sieve_segment (default 1024)
  *   "entry_hits" target marks per lane-task for medium primes (1..4096)
  *   "tail_cap"   capacity of the per-call list of n unresolved in LDS
@@ -250,8 +254,9 @@ void esq_batch_destroy(esq_batch *batch);
  *                (esq_phase_take); costs a few atomics per segment
  *   "medium_max" largest prime whose multiples every segment marks itself
  *                (11..11000); larger primes go through per-segment hit slots
- *   "bucket_cap" hit slots per segment (0 = sized from the expected count);
- *                a segment whose slots overflow marks those primes directly
+ *   "bucket_cap" hit slots per segment (0 = sized from the expected count; the
+ *                segments 4096 shorter have a few less, for the same total); a
+ *                segment whose slots overflow marks those primes directly
  *   "items_per_wg" batched form: work items (runs of consecutive segments)
  *                per resident workgroup
  *   "runs_per_wg" single interval: runs of consecutive segments per resident
