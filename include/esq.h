@@ -258,7 +258,8 @@ void esq_batch_destroy(esq_batch *batch);
  *                segments 4096 shorter have a few less, for the same total); a
  *                segment whose slots overflow marks those primes directly
  *   "items_per_wg" batched form: work items (runs of consecutive segments)
- *                per resident workgroup
+ *                per resident workgroup (default 4, of which aggregates-only
+ *                batches make up to 12 where that leaves runs of 16 segments)
  *   "runs_per_wg" single interval: runs of consecutive segments per resident
  *                workgroup (1..64; at 1, aggregates-only calls of 24 segments
  *                a workgroup or more cut the last quarter into short runs)

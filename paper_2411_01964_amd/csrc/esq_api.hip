@@ -778,31 +778,6 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     // set the scratch's size there is one, as there is no room to take
     const uint32_t n_acc = n_iv == 1 && mode != 2 && par.bucket_cap == 0 && par.tail_cap <= Params().tail_cap
                                ? kAccCopies : n_iv;
-    uint32_t cap = 0;
-    if (any_bucket) {
-        const double density = c->inv_pref[pmax_end_all] - c->inv_pref[med_end];
-        auto slots = [&](uint64_t region) {
-            const uint32_t n = (uint32_t)std::ceil(8.0 * (double)region * density + 32.0);
-            return par.bucket_cap > 0 ? (uint32_t)par.bucket_cap : (n + 7) & ~7u;
-        };
-        // The column layout has 1.6% more segments (its region holds the halo
-        // too): they share the row layout's slots, so that no call needs more
-        // scratch than that layout would and a limit on it (the static array
-        // of esq_verify_range_noalloc, a server's budget) admits the same calls
-        // (64 words for the alignment between the two, in calls of that size).
-        // The copies of the accumulators come out of the slots likewise.
-        const bool large = nseg_total >= 1024;
-        const uint64_t copies = large ? 64 + (n_acc - n_iv) * sizeof(Acc) / 4 : 0;
-        auto less_copies = [&](uint64_t n, uint32_t slots_row) {
-            return n_acc > n_iv ? slots_per_segment(n, slots_row, n, copies) : slots_row;
-        };
-        if (col)
-            cap = slots_per_segment(nseg_row, less_copies(nseg_row, slots((1u << kColLog2) + kColHalo)),
-                                    nseg_total, 4 * P->ranges.size() + (large ? 64 : 0));
-        else
-            cap = less_copies(nseg_total, slots(R));
-    }
-
     // LDS of the segment kernel: bitmap + medium-prime tables (+ tasks if they fit)
     const uint32_t nmed = med_end - kFirstMedium;
     const uint32_t n_tasks = mt ? mt->n_tasks : 0;
@@ -853,7 +828,15 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
             nseg_total, std::max<uint64_t>(resident * (uint64_t)par.runs_per_wg,
                                            (nseg_total + kFlushSegs - 1) / kFlushSegs));
     } else {
-        const uint64_t target = std::max<uint64_t>(1, resident * (uint64_t)par.items_per_wg);
+        // In the column layout a run's own start is cheap enough for runs of
+        // about 16 segments, four to twelve a workgroup (us per batch with 4 and
+        // 8 and 12 a workgroup: 64 intervals, 10 segments a workgroup 93, 104,
+        // 147; 1024, 113 segments 610, 587, 595; 4096, 525 segments 2580, 2425,
+        // 2392).  A knob off its default is taken as it is.
+        uint64_t per = (uint64_t)par.items_per_wg;
+        if (col && par.items_per_wg == Params().items_per_wg)
+            per = std::min<uint64_t>(12, std::max<uint64_t>(per, per_wg / 16));
+        const uint64_t target = std::max<uint64_t>(1, resident * per);
         const uint64_t run = std::min<uint64_t>(
             kFlushSegs, std::max<uint64_t>(1, (nseg_total + target - 1) / target));
         for (uint32_t i = 0; i < n_iv; i++)
@@ -867,6 +850,31 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
             }
         n_items = (uint32_t)items.size();
     }
+    uint32_t cap = 0;
+    if (any_bucket) {
+        const double density = c->inv_pref[pmax_end_all] - c->inv_pref[med_end];
+        auto slots = [&](uint64_t region) {
+            const uint32_t n = (uint32_t)std::ceil(8.0 * (double)region * density + 32.0);
+            return par.bucket_cap > 0 ? (uint32_t)par.bucket_cap : (n + 7) & ~7u;
+        };
+        // The column layout has 1.6% more segments (its region holds the halo
+        // too): they share the row layout's slots, so that no call needs more
+        // scratch than that layout would and a limit on it (the static array
+        // of esq_verify_range_noalloc, a server's budget) admits the same calls
+        // (64 words for the alignment between the two, in calls of that size).
+        // The copies of the accumulators come out of the slots likewise.
+        const bool large = nseg_total >= 1024;
+        const uint64_t copies = large ? 64 + (n_acc - n_iv) * sizeof(Acc) / 4 : 0;
+        auto less_copies = [&](uint64_t n, uint32_t slots_row) {
+            return n_acc > n_iv ? slots_per_segment(n, slots_row, n, copies) : slots_row;
+        };
+        if (col)
+            cap = slots_per_segment(nseg_row, less_copies(nseg_row, slots((1u << kColLog2) + kColHalo)),
+                                    nseg_total, 4 * (P->ranges.size() + items.size()) + (large ? 64 : 0));
+        else
+            cap = less_copies(nseg_total, slots(R));
+    }
+
     // no tail pass when the search limit is the in-LDS depth: the list then
     // only holds exceptions, and only when the call lists them
     const bool no_tail = klds >= kmax_eff;
