@@ -262,7 +262,7 @@ void esq_batch_destroy(esq_batch *batch);
  *                batches make up to 12 where that leaves runs of 16 segments)
  *   "runs_per_wg" single interval: runs of consecutive segments per resident
  *                workgroup (1..64; at 1, aggregates-only calls of 24 segments
- *                a workgroup or more cut the last quarter into short runs)
+ *                a workgroup or more cut the last half into short runs)
  *   "stagger"    segment kernel, summary mode: start delay of each
  *                later-launched quarter of the workgroups, in units of 64
  *                clocks (0..4096; 0 = none; default 72, about a quarter of a

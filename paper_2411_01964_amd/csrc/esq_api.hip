@@ -810,14 +810,17 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     uint32_t n_items = 0, run_long = 0, run_short = 0;
     const uint64_t per_wg = nseg_total / resident;
     if (n_iv == 1 && col && par.runs_per_wg == 1 && per_wg >= 24) {
-        // One long run per resident workgroup, then the last quarter in short
+        // One long run per resident workgroup, then the other half in short
         // runs from the queue: workgroups that share a CU drift apart by a
         // tenth of the kernel's time, and equal runs leave the CUs part empty
         // at the end.  Below 24 segments a workgroup a run's own start (first
-        // hits, queue: about one segment's time) costs what the balance gives
-        // (2^32 odd n: 105 us equal, 115 us cut; 2^33: 181 us equal, 174 us cut).
-        run_long = (uint32_t)std::min<uint64_t>(kFlushSegs, per_wg * 3 / 4);
-        run_short = (uint32_t)std::min<uint64_t>(kFlushSegs, per_wg / 12);
+        // hits, queue) costs what the balance gives (16 segments a workgroup:
+        // 90 us equal, 98 cut).  By segments a workgroup, long runs of three
+        // quarters and short ones of a twelfth / of a half and a sixth / an
+        // eighth: 24 134, 134, 135 us; 33 165, 162.6, 164.5; 49 227, 222, 219;
+        // 132 581, 568, 553.
+        run_long = (uint32_t)std::min<uint64_t>(kFlushSegs, per_wg / 2);
+        run_short = (uint32_t)std::min<uint64_t>(kFlushSegs, per_wg / (per_wg < 40 ? 6 : 8));
         const uint64_t rest = nseg_total - resident * run_long;
         n_items = (uint32_t)(resident + (rest + run_short - 1) / run_short);
     } else if (n_iv == 1) {

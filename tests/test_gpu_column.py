@@ -66,7 +66,7 @@ def test_high_interval_equals_the_row_layout(kw):
 
 
 def test_short_runs_from_the_queue():
-    """2^33 odd n: about 33 segments per resident workgroup, the last quarter
+    """2^33 odd n: about 33 segments per resident workgroup, the last half
     of them in short runs."""
     lo = (1 << 50) - (1 << 34) - (1 << 20) + 1
     g = esq.verify_range(lo, lo + (1 << 34) + 2 * 31)
