@@ -709,7 +709,7 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
             const uint64_t jmax = m_hi / (pc * pc);
             v.n_cof = (uint32_t)((jmax + 1) / 2);
             // cofactor j's range holds about L / (2 sqrt(m j) ln p) primes:
-            // the j with more than 4 share them over 8 lanes
+            // the j with more than 4 share them over kCofactorLanes lanes
             const double m_lo = std::max(1.0, 2.0 * (double)B0 + 1);
             v.sqrt_lo = std::sqrt(m_lo);
             v.sqrt_hi = std::sqrt((double)m_hi);
@@ -722,7 +722,7 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
         if (v.pmax_end > med_end)
             any_bucket = true;
         max_direct = std::max(max_direct, v.b_direct_end - med_end);
-        max_cof = std::max(max_cof, v.n_cof + 7 * v.n_cof_wide);  // cofactor threads
+        max_cof = std::max(max_cof, v.n_cof + (kCofactorLanes - 1) * v.n_cof_wide);  // cofactor threads
         E_max = std::max(E_max, (uint64_t)(v.nseg - 1) * S + R);
     }
     // Workgroups of k_bucket_own: one per CU where the intervals allow, each

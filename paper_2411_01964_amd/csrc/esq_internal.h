@@ -57,6 +57,7 @@ constexpr uint32_t kFinalizeSortCap = 16384;  // LDS sort capacity of the finali
 constexpr uint32_t kAccCopies = 16;       // of one interval's accumulators (a power of two)
 constexpr uint32_t kOwnSegs = 256;        // segments per workgroup of k_bucket_own, at most
 constexpr uint64_t kCofactorPrime = 1u << 20; // largest direct/cofactor cut-over considered
+constexpr uint32_t kCofactorLanes = 16;   // lanes of a cofactor with a wide range of primes
 
 // Per-interval accumulators in device scratch.  A launch of one interval has
 // kAccCopies of them: workgroup b adds its counts and least n to copy b mod
@@ -86,7 +87,7 @@ struct Interval {
     uint64_t* out_bits;     // sieve output words, or null
     uint32_t out_shift;     // sieve: I0 - A0
     double sqrt_lo, sqrt_hi; // square roots of the least and the largest odd number of its regions
-    uint32_t n_cof_wide;    // the first n_cof_wide cofactors (widest ranges) take 8 lanes each
+    uint32_t n_cof_wide;    // the first n_cof_wide cofactors (widest ranges) take kCofactorLanes lanes each
 };
 
 // Medium-prime lane-task, packed in a uint2: x = v q | (idx << 21), y = c q;

@@ -252,52 +252,65 @@ __device__ __forceinline__ double recip_d(double q)
 // Segment s of an interval covers region offsets y in [s S, s S + R): a hit
 // belongs to segment floor(y / S) and to each earlier segment still reaching it.
 // A hit's slot number comes back from a device-scope atomic, microseconds
-// later: the hits y, y + step, ... < E go out kEmit at a time.
-constexpr int kEmit = 4;
-__device__ __forceinline__ void bucket_emit(const Launch& L, uint32_t seg_base, uint32_t nseg, uint64_t y,
-                                            uint64_t step, uint64_t E)
+// later: the hits go out kEmit at a time (y[0 .. n)).
+constexpr uint32_t kEmit = 4;
+__device__ __forceinline__ void bucket_put(const Launch& L, uint32_t seg_base, uint32_t nseg,
+                                           const uint64_t (&y)[kEmit], uint32_t n)
 {
     const uint64_t S = L.S;
     const uint32_t R = L.rw * 64;
-    while (y < E) {
-        uint64_t seg[kEmit];
-        uint32_t off[kEmit], pos[kEmit];
-        bool again = false;
+    uint64_t seg[kEmit];
+    uint32_t off[kEmit], pos[kEmit];
+    bool again = false;
 #pragma unroll
-        for (int u = 0; u < kEmit; u++) {
-            const uint64_t yu = y + u * step;
-            // y div S through the reciprocal: at most one too small (y < 2^56)
-            seg[u] = __umul64hi(yu, L.s_inv);
-            off[u] = (uint32_t)(yu - seg[u] * S);
-            if (off[u] >= S) {
-                seg[u]++;
-                off[u] -= (uint32_t)S;
-            }
-            const bool in = yu < E;
-            again = again || (in && off[u] + S < R);
-            pos[u] = ~0u;
-            if (in && seg[u] < nseg)
-                pos[u] = atomicAdd(&L.bucket_cnt[seg_base + seg[u]], 1u);
-            else if (!in)
-                seg[u] = 0;
+    for (uint32_t u = 0; u < kEmit; u++) {
+        // y div S through the reciprocal: at most one too small (y < 2^56)
+        seg[u] = __umul64hi(y[u], L.s_inv);
+        off[u] = (uint32_t)(y[u] - seg[u] * S);
+        if (off[u] >= S) {
+            seg[u]++;
+            off[u] -= (uint32_t)S;
         }
+        const bool in = u < n;
+        again = again || (in && off[u] + S < R);
+        pos[u] = ~0u;
+        if (in && seg[u] < nseg)
+            pos[u] = atomicAdd(&L.bucket_cnt[seg_base + seg[u]], 1u);
+        else if (!in)
+            seg[u] = 0;
+    }
 #pragma unroll
-        for (int u = 0; u < kEmit; u++)
-            if (pos[u] < L.bucket_cap)
-                L.bucket_slot[(seg_base + seg[u]) * L.bucket_cap + pos[u]] = off[u];
-        if (again)  // hits in the overlap with earlier segments
-            for (int u = 0; u < kEmit; u++) {
-                uint64_t g = seg[u];
-                uint64_t o = off[u] + S;
-                while (y + u * step < E && o < R && g > 0) {
-                    g--;
-                    const uint32_t at = atomicAdd(&L.bucket_cnt[seg_base + g], 1u);
-                    if (at < L.bucket_cap)
-                        L.bucket_slot[(seg_base + g) * L.bucket_cap + at] = (uint32_t)o;
-                    o += S;
-                }
+    for (uint32_t u = 0; u < kEmit; u++)
+        if (pos[u] < L.bucket_cap)
+            L.bucket_slot[(seg_base + seg[u]) * L.bucket_cap + pos[u]] = off[u];
+    if (again)  // hits in the overlap with earlier segments
+        for (uint32_t u = 0; u < kEmit; u++) {
+            uint64_t g = seg[u];
+            uint64_t o = off[u] + S;
+            while (u < n && o < R && g > 0) {
+                g--;
+                const uint32_t at = atomicAdd(&L.bucket_cnt[seg_base + g], 1u);
+                if (at < L.bucket_cap)
+                    L.bucket_slot[(seg_base + g) * L.bucket_cap + at] = (uint32_t)o;
+                o += S;
             }
-        y += kEmit * step;
+        }
+}
+
+// the hits y, y + step, ... < E
+__device__ __forceinline__ void bucket_emit(const Launch& L, uint32_t seg_base, uint32_t nseg, uint64_t y0,
+                                            uint64_t step, uint64_t E)
+{
+    while (y0 < E) {
+        uint64_t y[kEmit];
+        uint32_t n = 0;
+#pragma unroll
+        for (uint32_t u = 0; u < kEmit; u++) {
+            y[u] = y0 + u * step;
+            n += y[u] < E ? 1u : 0u;
+        }
+        bucket_put(L, seg_base, nseg, y, n);
+        y0 += kEmit * step;
     }
 }
 
@@ -316,14 +329,18 @@ __device__ __forceinline__ bool cofactor_range(uint64_t j, double sqrt_lo, doubl
     return *hi_d >= *lo_d && *hi_d >= (double)p_cof;
 }
 
-// hit(y) for the region offset y of each of j's multiples of a prime p >= p_cof
-// in that range, by lanes g, g + lanes, ...; the regions' bit 0 is odd index B0
-// and they hold E bits.  The range's ends come from the estimates by exact
-// corrections; a p is looked up in the bitmap of odd primes (one load, where a
-// search in the prime table is a chain of them).
-template <typename Hit>
+// hits(y, n) for the region offsets y[0 .. n) of j's multiples of the primes p >=
+// p_cof in that range, at most kEmit of them a call; the regions' bit 0 is odd
+// index B0 and they hold E bits.  The range's ends come from the estimates by
+// exact corrections.  Its primes come from the bitmap of odd primes, of which
+// lane g takes words g, g + lanes, ... of the range's: one load for 32 odd
+// numbers.  What bounds a wide range is the chain of a lane's loads and of the
+// hits' atomics.  2^30 odd n from 2^40, where j = 1 has a range of 1024 numbers:
+// k_bucket 46 us a number a load and a hit at a time over 8 lanes, 16 a word a
+// load, 9 over 16 lanes with four hits in flight.
+template <typename Hits>
 __device__ __forceinline__ void cofactor_hits(const Launch& L, uint64_t j, double lo_d, double hi_d, int64_t B0,
-                                              uint64_t E, uint32_t p_cof, uint32_t g, uint32_t lanes, Hit hit)
+                                              uint64_t E, uint32_t p_cof, uint32_t g, uint32_t lanes, Hits hits)
 {
     const uint64_t m_lo = B0 > 0 ? 2 * (uint64_t)B0 + 1 : 1;
     const uint64_t m_hi = 2 * (uint64_t)(B0 + (int64_t)E - 1) + 1;
@@ -336,9 +353,27 @@ __device__ __forceinline__ void cofactor_hits(const Launch& L, uint64_t j, doubl
     while (j * pb * pb > m_hi)
         pb--;
     pb = min(pb, (uint64_t)L.plimit);
-    for (uint64_t p = (max(pa, (uint64_t)p_cof) | 1) + 2 * g; p <= pb; p += 2 * lanes)
-        if (L.pbits[p >> 6] >> ((p >> 1) & 31u) & 1u)
-            hit((j * p * p - 1) / 2 - (uint64_t)B0);
+    const uint64_t a = max(pa, (uint64_t)p_cof) | 1, w_end = pb >> 6;
+    for (uint64_t w = (a >> 6) + g; w <= w_end; w += lanes) {
+        // bit b: 64 w + 2 b + 1; those from a on, and up to pb
+        uint32_t bits = L.pbits[w];
+        if (w == a >> 6)
+            bits &= ~0u << ((a >> 1) & 31u);
+        if (w == w_end)
+            bits &= (uint32_t)((1ull << (((pb & 63u) + 1) >> 1)) - 1);
+        while (bits) {
+            uint64_t y[kEmit];
+            uint32_t n = 0;
+#pragma unroll
+            for (uint32_t u = 0; u < kEmit; u++) {
+                n += bits ? 1u : 0u;
+                const uint64_t p = 64 * w + 2 * (uint64_t)(31 - __clz((int)(bits | 1u))) + 1;
+                y[u] = (j * p * p - 1) / 2 - (uint64_t)B0;
+                bits &= ~(1u << (31 - __clz((int)(bits | 1u))));
+            }
+            hits(y, n);
+        }
+    }
 }
 
 // Few segments: grid.y = interval.  Work units, in order: kHeavyLanes-wide
@@ -348,7 +383,6 @@ __device__ __forceinline__ void cofactor_hits(const Launch& L, uint64_t j, doubl
 // (p_cof and up), kCofactorLanes lanes for each of the first n_cof_wide odd
 // cofactors j (wide ranges) and one thread for each remaining j.
 constexpr uint32_t kHeavyLanes = 64;
-constexpr uint32_t kCofactorLanes = 8;
 
 __global__ __launch_bounds__(256) void k_bucket(Launch L, uint32_t n_heavy, uint32_t max_direct, uint32_t p_cof,
                                                 int in_doubles)
@@ -386,7 +420,7 @@ __global__ __launch_bounds__(256) void k_bucket(Launch L, uint32_t n_heavy, uint
     if (cofactor_range(2 * c + 1, iv->sqrt_lo, iv->sqrt_hi, p_cof, &lo_d, &hi_d))
         cofactor_hits(L, 2 * c + 1, lo_d, hi_d, B0, E, p_cof, wide ? (uint32_t)(tc % kCofactorLanes) : 0u,
                       wide ? kCofactorLanes : 1u,
-                      [&](uint64_t y) { bucket_emit(L, iv->seg_base, iv->nseg, y, E, y + 1); });
+                      [&](const uint64_t (&y)[kEmit], uint32_t n) { bucket_put(L, iv->seg_base, iv->nseg, y, n); });
 }
 
 // Many segments: a workgroup owns up to kOwnSegs consecutive segments of one
@@ -458,7 +492,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
     auto cofactor = [&](uint32_t c) {
         double lo_d, hi_d;
         if (cofactor_range(2 * (uint64_t)c + 1, sqrt_lo, sqrt_hi, p_cof, &lo_d, &hi_d))
-            cofactor_hits(L, 2 * (uint64_t)c + 1, lo_d, hi_d, B0, E, p_cof, 0u, 1u, emit);
+            cofactor_hits(L, 2 * (uint64_t)c + 1, lo_d, hi_d, B0, E, p_cof, 0u, 1u,
+                          [&](const uint64_t (&y)[kEmit], uint32_t m) {
+                              for (uint32_t u = 0; u < kEmit; u++)
+                                  if (u < m)
+                                      emit(y[u]);
+                          });
     };
     for (uint32_t c = threadIdx.x; c < n_cof; c += blockDim.x) {
         double lo_d, hi_d;
