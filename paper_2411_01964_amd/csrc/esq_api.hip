@@ -1675,8 +1675,10 @@ int esq_set_param(const char* name, int64_t value)
     } else {
         return fail(ESQ_EINVAL, "unknown parameter " + n);
     }
+    // the knobs that the segment length, and so the tables, depend on
+    // (tail_cap: see seg_log2_for)
     if (g_ctx && (n == "seg_log2" || n == "kh" || n == "medium_max" || n == "entry_hits" ||
-                  n == "block" || n == "per_n_block")) {
+                  n == "block" || n == "per_n_block" || n == "tail_cap")) {
         hipError_t e = hipSetDevice(g_ctx->device);
         if (e != hipSuccess)
             return hip_fail(e, "hipSetDevice");

@@ -1,0 +1,39 @@
+"""Knobs that decide which tables a call needs and how its work is cut: tables
+are resident whatever order the knobs were set in, and a knob set off its
+default is taken as it is."""
+import pytest
+import torch
+
+from paper_2411_01964_amd import esq
+from tests.test_gpu_parity import DEFAULTS, MAX_HI, knobs
+from tests.test_zz_no_alloc import KEYS, noalloc_call
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module", autouse=True)
+def lib_ready():
+    esq.init(0, MAX_HI)
+    knobs()
+    yield
+    for k, v in DEFAULTS.items():
+        esq.set_param(k, v)
+
+
+@pytest.mark.parametrize("n,kmax,per_n", [(5003, 0, True), (1 << 21, 0, True), (70001, 3, False),
+                                          (1 << 24, 4, False)])
+def test_noalloc_after_a_longer_tail_list_was_taken_back(n, kmax, per_n):
+    """A tail list above its default keeps launches at the knob's segment
+    length; back at the default, short ones take shorter segments, whose tables
+    the no-alloc call needs resident.  (A medium_max of its own, so that no
+    other test has made them.)"""
+    esq.set_param("tail_cap", 1 << 21)
+    esq.set_param("medium_max", 3571 + n % 97)
+    esq.set_param("tail_cap", 1 << 20)
+    lo = (1 << 44) + 12345
+    got = noalloc_call(lo, lo + 2 * n, kmax, per_n, 16)
+    want = esq.verify_range(lo, lo + 2 * n, kmax=kmax, per_n=per_n, exceptions_cap=16)
+    assert all(got[k] == want[k] for k in KEYS)
+    if per_n:
+        assert torch.equal(got["per_n"], want["per_n"])
+    knobs()
