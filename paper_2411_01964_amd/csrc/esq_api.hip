@@ -520,24 +520,29 @@ uint32_t block_for(const Params& par, int mode, uint32_t n_iv, int log2S, uint64
     return (uint32_t)(few ? std::min(b, 512) : b);
 }
 
-// The medium-prime tables of the verify geometries for the current knobs
-// (summary, per-n, and summary with a bounded search, at every segment length
-// that seg_log2_for may take), made at set-up (esq_init, esq_set_param; g_mu
-// held) so that calls find them resident.
-int prebuild_med_table(Ctx* c, const Params& par)
+// The medium-prime tables of the geometries of the current knobs (summary,
+// per-n, summary with a bounded search, and the sieve alone, at every segment
+// length that seg_log2_for may take), made at set-up (esq_init, esq_set_param;
+// g_mu held) so that calls find them resident: making one allocates, copies and
+// waits for the device.
+int prebuild_med_tables(Ctx* c, const Params& par)
 {
     const uint32_t med_end = medium_end(c, par);
     if (med_end <= kFirstMedium)
         return ESQ_OK;
     MedTable* mt = nullptr;
-    for (int v = 0; v < 3; v++) {
-        const int mode = v == 1 ? 1 : 0;
-        const uint32_t klds = v == 2 ? 1u : (uint32_t)par.kh;
-        for (int s = seg_log2_for(par, mode, klds, 0, 1); s <= par.seg_log2; s++) {
-            const Geometry g = geometry(par, mode, klds, s);
+    const struct {
+        int mode;
+        uint32_t klds;
+        int log2S;  // the longest segments
+    } forms[] = {{0, (uint32_t)par.kh, par.seg_log2}, {1, (uint32_t)par.kh, par.seg_log2},
+                 {0, 1u, par.seg_log2}, {2, 0u, par.sieve_seg_log2}};
+    for (const auto& f : forms) {
+        for (int s = seg_log2_for(par, f.mode, f.klds, 0, 1); s <= f.log2S; s++) {
+            const Geometry g = geometry(par, f.mode, f.klds, s);
             for (int large = 0; large < 2; large++) {  // block sizes of short and long launches
                 const int rc = get_med_table_locked(c, g.rw, g.S, g.col, med_end, (uint32_t)par.entry_hits,
-                                                    block_for(par, mode, 1, s, large ? ~0ull : 0), &mt);
+                                                    block_for(par, f.mode, 1, s, large ? ~0ull : 0), &mt);
                 if (rc)
                     return rc;
             }
@@ -1341,7 +1346,7 @@ int esq_init(int device, uint64_t max_hi)
     }
     c->max_hi = std::max(c->max_hi, max_hi);
     // the medium-prime tables of the current knobs (they need the primes)
-    int rc = prebuild_med_table(c, g_par);
+    int rc = prebuild_med_tables(c, g_par);
     if (rc)
         return rc;
     if ((e = hipDeviceSynchronize()) != hipSuccess)
@@ -1678,11 +1683,12 @@ int esq_set_param(const char* name, int64_t value)
     // the knobs that the segment length, and so the tables, depend on
     // (tail_cap: see seg_log2_for)
     if (g_ctx && (n == "seg_log2" || n == "kh" || n == "medium_max" || n == "entry_hits" ||
-                  n == "block" || n == "per_n_block" || n == "tail_cap")) {
+                  n == "block" || n == "per_n_block" || n == "sieve_seg_log2" || n == "sieve_block" ||
+                  n == "tail_cap")) {
         hipError_t e = hipSetDevice(g_ctx->device);
         if (e != hipSuccess)
             return hip_fail(e, "hipSetDevice");
-        return prebuild_med_table(g_ctx, g_par);
+        return prebuild_med_tables(g_ctx, g_par);
     }
     return ESQ_OK;
 }

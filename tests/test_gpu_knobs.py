@@ -37,3 +37,23 @@ def test_noalloc_after_a_longer_tail_list_was_taken_back(n, kmax, per_n):
     if per_n:
         assert torch.equal(got["per_n"], want["per_n"])
     knobs()
+
+
+@pytest.mark.parametrize("n", [1000, (1 << 21) + 13, (1 << 23) + 1, 1 << 26])
+def test_a_sieve_call_of_a_new_length_waits_for_nothing(n):
+    """Calls only enqueue: the first sieve of a segment length returns while
+    work queued before it still runs (making its tables would wait for it)."""
+    knobs(medium_max=3300 + n % 89)
+    lo, span = (1 << 49) + 1, 1 << 39
+    esq.verify_range(lo, lo + span)            # the stream's scratch block
+    out = torch.empty((n + 63) // 64, dtype=torch.int64, device="cuda")
+    torch.cuda.synchronize()
+    for _ in range(10):                        # 5 ms of work each
+        esq.verify_range_async(lo, lo + span)
+    queued = torch.cuda.Event()
+    queued.record()
+    esq.sieve_segment(lo, lo + 2 * n, out=out)
+    assert not queued.query()
+    torch.cuda.synchronize()
+    assert queued.query()
+    knobs()
