@@ -592,9 +592,12 @@ uint32_t slots_per_segment(uint64_t n_row, uint32_t cap_row, uint64_t n, uint64_
     return words > extra + 2 * n ? (uint32_t)((words - extra) / n - 1) : 1u;
 }
 
-// Plan one launch over `reqs` (mode 0/1 verify, 2 sieve).
+// Plan one launch over `reqs` (mode 0/1 verify, 2 sieve).  sizes_only: for the
+// scratch layout alone, without descriptors and the division of the large
+// primes' work, whose searches in the prime table are most of a plan's time (300
+// intervals: two plans 52 us, two layouts 9; 4096: 900 and 76).
 int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<Req>& reqs,
-         bool exc_list, Planned* P, bool no_alloc = false)
+         bool exc_list, Planned* P, bool no_alloc = false, bool sizes_only = false)
 {
     const uint32_t n_iv = (uint32_t)reqs.size();
     const uint32_t kmax_eff = kmax ? kmax : 63;
@@ -680,7 +683,7 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     const uint32_t all_end = std::max(med_end, prime_upper(c, pmax_all));
     const bool own = all_end > med_end && (double)nseg_total * (double)R *
                                               (c->inv_pref[all_end] - c->inv_pref[med_end]) >= kOwnMinHits;
-    if (own || direct_threads_full > (uint64_t)c->n_cu * 2048) {
+    if (!sizes_only && (own || direct_threads_full > (uint64_t)c->n_cu * 2048)) {
         double best = 0;
         for (int h = 20; h <= 40; h++) {
             const uint64_t cand = (uint64_t)std::ldexp(1.0, h / 2) * (h % 2 ? 1.41421356 : 1.0);
@@ -696,15 +699,13 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     }
     const uint32_t direct_end = prime_upper(c, P0);
     uint32_t max_direct = 0, max_cof = 0;
-    bool any_bucket = false;
-    uint32_t pmax_end_all = med_end;
+    const bool any_bucket = all_end > med_end;
     uint64_t E_max = 0;
-    for (uint32_t i = 0; i < n_iv; i++) {
+    for (uint32_t i = 0; i < n_iv && !sizes_only; i++) {
         Interval& v = ivs[i];
         if (!v.nseg)
             continue;
         v.pmax_end = std::max(prime_upper(c, pmax[i]), med_end);
-        pmax_end_all = std::max(pmax_end_all, v.pmax_end);
         v.b_direct_end = std::max(med_end, std::min(v.pmax_end, direct_end));
         if (v.pmax_end > v.b_direct_end) {
             const int64_t B0 = v.A0 - (int64_t)hlo * 64 - (mode == 2 ? 0 : 1);  // region bit 0
@@ -724,8 +725,6 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
             const double j_wide = (per_j / 4.0) * (per_j / 4.0);
             v.n_cof_wide = (uint32_t)std::min<double>(v.n_cof, std::floor((j_wide + 1) / 2));
         }
-        if (v.pmax_end > med_end)
-            any_bucket = true;
         max_direct = std::max(max_direct, v.b_direct_end - med_end);
         max_cof = std::max(max_cof, v.n_cof + (kCofactorLanes - 1) * v.n_cof_wide);  // cofactor threads
         E_max = std::max(E_max, (uint64_t)(v.nseg - 1) * S + R);
@@ -742,7 +741,7 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
         for (uint32_t i = 0; i < n_iv; i++) {
             const uint64_t parts = (ivs[i].nseg + share - 1) / share;
             n_ranges += parts;
-            for (uint64_t k = 0; k < parts && n_iv > 1; k++) {
+            for (uint64_t k = 0; k < parts && n_iv > 1 && !sizes_only; k++) {
                 uint4 r;
                 r.x = i;
                 r.y = (uint32_t)(k * ivs[i].nseg / parts);
@@ -756,7 +755,7 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     // k_bucket: primes with more than 8 hits in the longest interval get a
     // group of lanes each
     uint32_t n_heavy = 0;
-    if (any_bucket) {
+    if (any_bucket && !sizes_only) {
         const uint32_t heavy_end = prime_upper(c, isqrt_u64(E_max / 8));
         n_heavy = heavy_end > med_end ? std::min(heavy_end - med_end, max_direct) : 0;
         max_direct -= n_heavy;
@@ -847,8 +846,9 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
         const uint64_t target = std::max<uint64_t>(1, resident * per);
         const uint64_t run = std::min<uint64_t>(
             kFlushSegs, std::max<uint64_t>(1, (nseg_total + target - 1) / target));
-        for (uint32_t i = 0; i < n_iv; i++)
-            for (uint64_t b = 0; b < ivs[i].nseg; b += run) {
+        for (uint32_t i = 0; i < n_iv; i++) {
+            n_items += (uint32_t)((ivs[i].nseg + run - 1) / run);
+            for (uint64_t b = 0; b < ivs[i].nseg && !sizes_only; b += run) {
                 uint4 x;
                 x.x = i;
                 x.y = (uint32_t)b;
@@ -856,11 +856,13 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
                 x.w = 0;
                 items.push_back(x);
             }
-        n_items = (uint32_t)items.size();
+        }
     }
+    // descriptors of several intervals' runs and ranges (one interval has none)
+    const size_t item_descs = n_iv > 1 ? n_items : 0, range_descs = n_iv > 1 ? P->n_ranges : 0;
     uint32_t cap = 0;
     if (any_bucket) {
-        const double density = c->inv_pref[pmax_end_all] - c->inv_pref[med_end];
+        const double density = c->inv_pref[all_end] - c->inv_pref[med_end];
         auto slots = [&](uint64_t region) {
             const uint32_t n = (uint32_t)std::ceil(8.0 * (double)region * density + 32.0);
             return par.bucket_cap > 0 ? (uint32_t)par.bucket_cap : (n + 7) & ~7u;
@@ -878,7 +880,7 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
         };
         if (col)
             cap = slots_per_segment(nseg_row, less_copies(nseg_row, slots((1u << kColLog2) + kColHalo)),
-                                    nseg_total, 4 * (P->ranges.size() + items.size()) + (large ? 64 : 0));
+                                    nseg_total, 4 * (range_descs + item_descs) + (large ? 64 : 0));
         else
             cap = less_copies(nseg_total, slots(R));
     }
@@ -895,9 +897,9 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     P->o_iv = off;
     off = align_up(off + sizeof(Interval) * std::max<uint32_t>(n_iv, 1));
     P->o_items = off;
-    off = align_up(off + sizeof(uint4) * items.size());
+    off = align_up(off + sizeof(uint4) * item_descs);
     P->o_ranges = off;
-    off = align_up(off + sizeof(uint4) * P->ranges.size());
+    off = align_up(off + sizeof(uint4) * range_descs);
     P->o_acc = off;
     off = align_up(off + sizeof(Acc) * std::max<uint32_t>(n_acc, 1));
     P->o_bcnt = off;
@@ -1484,7 +1486,7 @@ int esq_scratch_bytes(uint32_t count, const uint64_t* lo, const uint64_t* hi, ui
     // summary and per-n launches may differ in segment length: the larger
     for (int mode = 0; mode < 2; mode++) {
         Planned P;
-        if ((rc = plan(c, par, mode, kmax, reqs, false, &P)))
+        if ((rc = plan(c, par, mode, kmax, reqs, false, &P, false, true)))
             return rc;
         *out_bytes = std::max<uint64_t>(*out_bytes, P.bytes);
     }
