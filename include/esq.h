@@ -255,8 +255,10 @@ void esq_batch_destroy(esq_batch *batch);
  *   "medium_max" largest prime whose multiples every segment marks itself
  *                (11..11000); larger primes go through per-segment hit slots
  *   "bucket_cap" hit slots per segment (0 = sized from the expected count; the
- *                segments 4096 shorter have a few less, for the same total); a
- *                segment whose slots overflow marks those primes directly
+ *                segments 4096 shorter have a few less, for the same total, and
+ *                so they have of a number set here where only that total fits
+ *                ESQ_NOALLOC_SCRATCH_MAX); a segment whose slots overflow marks
+ *                those primes directly
  *   "items_per_wg" batched form: work items (runs of consecutive segments)
  *                per resident workgroup (default 4, of which aggregates-only
  *                batches make up to 12 where that leaves runs of 16 segments)

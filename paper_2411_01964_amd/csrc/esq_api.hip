@@ -892,29 +892,45 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
                                   ? 1 : std::max<uint64_t>(1, (uint64_t)par.tail_cap);
 
     // scratch layout, one allocation
-    size_t off = 0;
-    // (the uploaded descriptors first and together: one copy)
-    P->o_iv = off;
-    off = align_up(off + sizeof(Interval) * std::max<uint32_t>(n_iv, 1));
-    P->o_items = off;
-    off = align_up(off + sizeof(uint4) * item_descs);
-    P->o_ranges = off;
-    off = align_up(off + sizeof(uint4) * range_descs);
-    P->o_acc = off;
-    off = align_up(off + sizeof(Acc) * std::max<uint32_t>(n_acc, 1));
-    P->o_bcnt = off;
-    off = align_up(off + (any_bucket ? nseg_total * 4 : 0));
-    P->o_bslot = off;
-    off = align_up(off + (any_bucket ? nseg_total * cap * 4 : 0));
-    P->o_misc = off;
-    off = align_up(off + 64);
-    P->o_tn = off;
-    off = align_up(off + tail_cap * 8);
-    P->o_tiv = off;
-    off = align_up(off + tail_cap * 4);
-    P->o_td = off;
-    off = align_up(off + tail_cap);
-    P->bytes = off;
+    auto lay_out = [&]() {
+        size_t off = 0;
+        // (the uploaded descriptors first and together: one copy)
+        P->o_iv = off;
+        off = align_up(off + sizeof(Interval) * std::max<uint32_t>(n_iv, 1));
+        P->o_items = off;
+        off = align_up(off + sizeof(uint4) * item_descs);
+        P->o_ranges = off;
+        off = align_up(off + sizeof(uint4) * range_descs);
+        P->o_acc = off;
+        off = align_up(off + sizeof(Acc) * std::max<uint32_t>(n_acc, 1));
+        P->o_bcnt = off;
+        off = align_up(off + (any_bucket ? nseg_total * 4 : 0));
+        P->o_bslot = off;
+        off = align_up(off + (any_bucket ? nseg_total * cap * 4 : 0));
+        P->o_misc = off;
+        off = align_up(off + 64);
+        P->o_tn = off;
+        off = align_up(off + tail_cap * 8);
+        P->o_tiv = off;
+        off = align_up(off + tail_cap * 4);
+        P->o_td = off;
+        off = align_up(off + tail_cap);
+        P->bytes = off;
+    };
+    lay_out();
+    // A number of slots set by the knob is taken as it is (at a few per segment
+    // one less sends half as many segments again to the direct marking), unless
+    // only the shared total fits the static array.
+    if (col && any_bucket && par.bucket_cap > 0) {
+        const uint32_t shared = cap;
+        const bool fits = P->bytes <= ESQ_NOALLOC_SCRATCH_MAX;
+        cap = (uint32_t)par.bucket_cap;
+        lay_out();
+        if (fits && P->bytes > ESQ_NOALLOC_SCRATCH_MAX) {
+            cap = shared;
+            lay_out();
+        }
+    }
 
     Launch& L = P->L;
     L = Launch();

@@ -57,3 +57,30 @@ def test_a_sieve_call_of_a_new_length_waits_for_nothing(n):
     torch.cuda.synchronize()
     assert queued.query()
     knobs()
+
+
+def test_hit_slots_of_every_segment_are_as_many_as_set():
+    """1000 whole segments of the column layout (985 of the row layout): 500
+    slots more, of 4 bytes, in each."""
+    span = 2 * 1000 * ((1 << 18) - 4096)
+    figure = {}
+    for slots in (500, 1000):
+        knobs(bucket_cap=slots)
+        figure[slots] = esq.scratch_bytes([(1 << 49) + 1], [(1 << 49) + 1 + span])
+    knobs()
+    assert abs(figure[1000] - figure[500] - 1000 * 500 * 4) <= 512      # alignment
+
+
+def test_hit_slots_set_give_way_where_only_the_shared_total_fits():
+    """As many segments as the row layout fits into the static array at 4096
+    slots: the no-alloc call takes them."""
+    knobs(bucket_cap=4096, block=256)
+    lo, a, b = (1 << 49) + 1, 1 << 20, 1 << 34
+    while b - a > 1:
+        mid = (a + b) // 2
+        a, b = (mid, b) if esq.scratch_bytes([lo], [lo + 2 * mid]) <= esq.ESQ_NOALLOC_SCRATCH_MAX else (a, mid)
+    row = esq.verify_range(lo, lo + 2 * a)
+    knobs(bucket_cap=4096)
+    got = noalloc_call(lo, lo + 2 * a)
+    assert all(got[k] == row[k] for k in KEYS)
+    knobs()
