@@ -247,7 +247,9 @@ void esq_batch_destroy(esq_batch *batch);
  *                which calls below 2^30 odd n take 512; per-n batches of
  *                several intervals use "block")
  *   "sieve_block" the same for esq_sieve_segment (default 1024)
- *   "entry_hits" target marks per lane-task for medium primes (1..4096)
+ *   "entry_hits" target marks per lane-task for medium primes (1..4096; default
+ *                12, at which the kernel of aggregates-only calls takes as few
+ *                as one task per thread allows: 9 at the default medium_max)
  *   "tail_cap"   capacity of the per-call list of n unresolved in LDS
  *   "profile"    1 = time each segment-kernel launch (esq_profile_take)
  *   "phase_clock" 1 = count the segment kernel's time per phase

@@ -295,7 +295,8 @@ uint32_t prime_upper(const Ctx* c, uint64_t x)
 // x = v q | i << 21 (v q < R < 2^21; i < 2^11) and y = c q, in the column
 // layout scaled as its marks step.
 //
-// Task e of the table is taken by thread e mod block.
+// entry_hits 0: as few marks per task as one task per thread allows.  Task e of
+// the table is taken by thread e mod block.
 int get_med_table_locked(Ctx* c, uint32_t rw, uint32_t S, bool col, uint32_t med_end, uint32_t entry_hits,
                          uint32_t block, MedTable** out)
 {
@@ -316,14 +317,12 @@ int get_med_table_locked(Ctx* c, uint32_t rw, uint32_t S, bool col, uint32_t med
         medq[i].x = (uint32_t)(p * p);
         medq[i].y = (uint32_t)(S % (p * p));
     }
-    // Column layout: only the primes with more than kColSingle marks have
-    // tasks, and these as few marks as one task per lane allows (a lane keeps
-    // its task in registers; a second round of tasks costs more than the
-    // marks that it takes from the first).
-    uint32_t n_multi = nmed, target = entry_hits;
-    if (col) {
+    // Column layout: only the primes with more than kColSingle marks have tasks.
+    uint32_t n_multi = nmed, target = entry_hits ? entry_hits : (uint32_t)Params().entry_hits;
+    if (col)
         for (n_multi = 0; n_multi < nmed && hits(n_multi) > kColSingle;)
             n_multi++;
+    if (entry_hits == 0) {
         auto count = [&](uint32_t t) {
             uint64_t n = 0;
             for (uint32_t i = 0; i < n_multi; i++)
@@ -505,6 +504,16 @@ int seg_log2_for(const Params& par, int mode, uint32_t klds, uint64_t n, uint32_
     return s;
 }
 
+// Marks per lane-task of a launch in the column layout or not (see
+// get_med_table_locked): the knob's, or, where that is the default, in the column
+// layout 0.  A lane keeps its task there in registers, and a second round of
+// tasks costs more than the marks that it takes from the first (2^33 odd n, 8
+// marks, two rounds: 175 us, 9 in one: 170).
+uint32_t entry_hits_for(const Params& par, bool col)
+{
+    return col && par.entry_hits == Params().entry_hits ? 0u : (uint32_t)par.entry_hits;
+}
+
 // Threads per workgroup of the segment kernel in a mode (0 summary, 1 per-n,
 // 2 sieve alone) for a launch of n_iv intervals: per-n batches of many (short)
 // intervals keep the summary block size, which keeps more workgroups resident;
@@ -541,7 +550,7 @@ int prebuild_med_tables(Ctx* c, const Params& par)
         for (int s = seg_log2_for(par, f.mode, f.klds, 0, 1); s <= f.log2S; s++) {
             const Geometry g = geometry(par, f.mode, f.klds, s);
             for (int large = 0; large < 2; large++) {  // block sizes of short and long launches
-                const int rc = get_med_table_locked(c, g.rw, g.S, g.col, med_end, (uint32_t)par.entry_hits,
+                const int rc = get_med_table_locked(c, g.rw, g.S, g.col, med_end, entry_hits_for(par, g.col),
                                                     block_for(par, f.mode, 1, s, large ? ~0ull : 0), &mt);
                 if (rc)
                     return rc;
@@ -767,12 +776,11 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
         if (no_alloc) {
             // only a table made at set-up: making one here would allocate
             std::lock_guard<std::mutex> lk(g_mu);
-            auto it = c->med.find(std::make_tuple(rw, geo.S, geo.col, med_end, (uint32_t)par.entry_hits,
-                                                  blk));
+            auto it = c->med.find(std::make_tuple(rw, geo.S, geo.col, med_end, entry_hits_for(par, col), blk));
             if (it == c->med.end())
                 return fail(ESQ_ENOMEM, "medium-prime tables for these knobs are not resident");
             mt = &it->second;
-        } else if ((rc = get_med_table(c, rw, geo.S, geo.col, med_end, (uint32_t)par.entry_hits,
+        } else if ((rc = get_med_table(c, rw, geo.S, geo.col, med_end, entry_hits_for(par, col),
                                        blk, &mt))) {
             return rc;
         }

@@ -84,3 +84,32 @@ def test_hit_slots_set_give_way_where_only_the_shared_total_fits():
     got = noalloc_call(lo, lo + 2 * a)
     assert all(got[k] == row[k] for k in KEYS)
     knobs()
+
+
+def marking_share(**kw):
+    """The marking phase's share of the segment kernel's time (phase clock), and
+    the aggregates, of 2^30 odd n."""
+    knobs(**kw)
+    lo = (1 << 49) + 12345
+    esq.set_param("phase_clock", 1)
+    try:
+        esq.phase_take()
+        r = esq.verify_range(lo, lo + (1 << 31))
+        ph = esq.phase_take()
+    finally:
+        esq.set_param("phase_clock", 0)
+        knobs()
+    return ph["mark"] / sum(ph.values()), r
+
+
+def test_marks_per_task_are_as_many_as_set():
+    """With 4096 marks a task the multiples of 17^2, 907 in a region, are one
+    lane's, where the default gives a lane about 9: the marking phase is most of
+    the kernel."""
+    share, r = marking_share()
+    for hits in (11, 13, 64):
+        assert marking_share(entry_hits=hits)[1] == r
+    slow, s = marking_share(entry_hits=4096)
+    print("marking: %.2f of the kernel, %.2f with 4096 marks a task" % (share, slow))
+    assert s == r
+    assert share < 0.5 < slow
