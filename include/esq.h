@@ -278,6 +278,10 @@ void esq_batch_destroy(esq_batch *batch);
  *   "priority"   segment kernel: 1 = raise the wave priority of workgroups
  *                with more of their run left (default; not in aggregates-only
  *                calls at the default seg_log2, kh and block), 0 = off
+ *   "adapt"      1 (default) = seg_log2, sieve_seg_log2, per_n_block, entry_hits,
+ *                items_per_wg and runs_per_wg at their defaults stand for what
+ *                is said above of calls by their size; 0 = they are taken as
+ *                they are set
  * Applies to calls made after it.  Returns ESQ_EINVAL for an unknown name
  * or a value out of range.
  */

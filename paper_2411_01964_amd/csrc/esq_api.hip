@@ -63,6 +63,10 @@ struct Params {
     int64_t stagger = 72;       // segment kernel: start delay per workgroup slot (x 64 clocks)
     int64_t priority = 1;       // segment kernel: wave priority from the share of the run left
     int64_t cof_weight = 60;    // large primes: cost of a cofactor thread, % of a first-hit thread
+    // 1: seg_log2, sieve_seg_log2, per_n_block, entry_hits, items_per_wg and
+    // runs_per_wg at their defaults stand for rules by a call's size (see
+    // seg_log2_for, block_for, entry_hits_for, plan); 0: they are taken as set
+    int64_t adapt = 1;
 };
 
 struct MedTable {
@@ -494,7 +498,7 @@ int seg_log2_for(const Params& par, int mode, uint32_t klds, uint64_t n, uint32_
 {
     const Params dflt;
     const int knob = mode == 2 ? par.sieve_seg_log2 : par.seg_log2;
-    if (knob != (mode == 2 ? dflt.sieve_seg_log2 : dflt.seg_log2) || par.tail_cap > dflt.tail_cap ||
+    if (!par.adapt || knob != (mode == 2 ? dflt.sieve_seg_log2 : dflt.seg_log2) || par.tail_cap > dflt.tail_cap ||
         column_layout(par, mode, klds))
         return knob;
     const uint64_t wanted = n_iv > 1 ? 256 : mode == 2 ? 64 : 128;
@@ -507,11 +511,12 @@ int seg_log2_for(const Params& par, int mode, uint32_t klds, uint64_t n, uint32_
 // Marks per lane-task of a launch in the column layout or not (see
 // get_med_table_locked): the knob's, or, where that is the default, in the column
 // layout 0.  A lane keeps its task there in registers, and a second round of
-// tasks costs more than the marks that it takes from the first (2^33 odd n, 8
-// marks, two rounds: 175 us, 9 in one: 170).
+// tasks costs more than the marks that it takes from the first (k_column for
+// 2^33 odd n: 8 marks, two rounds 167.5 us, 9 in one round 154.7, 16 156.7, 24
+// 168).
 uint32_t entry_hits_for(const Params& par, bool col)
 {
-    return col && par.entry_hits == Params().entry_hits ? 0u : (uint32_t)par.entry_hits;
+    return col && par.adapt && par.entry_hits == Params().entry_hits ? 0u : (uint32_t)par.entry_hits;
 }
 
 // Threads per workgroup of the segment kernel in a mode (0 summary, 1 per-n,
@@ -525,7 +530,7 @@ uint32_t block_for(const Params& par, int mode, uint32_t n_iv, int log2S, uint64
     const int b = mode == 2 ? par.sieve_block : mode == 1 && n_iv == 1 ? par.per_n_block : par.block;
     const int knob = mode == 2 ? par.sieve_seg_log2 : par.seg_log2;
     const bool few = (log2S < knob && log2S <= (mode == 2 ? 17 : 16)) ||
-                     (mode == 1 && n < (1ull << 30) && par.per_n_block == Params().per_n_block);
+                     (mode == 1 && par.adapt && n < (1ull << 30) && par.per_n_block == Params().per_n_block);
     return (uint32_t)(few ? std::min(b, 512) : b);
 }
 
@@ -821,7 +826,7 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     items.clear();
     uint32_t n_items = 0, run_long = 0, run_short = 0;
     const uint64_t per_wg = nseg_total / resident;
-    if (n_iv == 1 && col && par.runs_per_wg == 1 && per_wg >= 24) {
+    if (n_iv == 1 && col && par.adapt && par.runs_per_wg == 1 && per_wg >= 24) {
         // One long run per resident workgroup, then the other half in short
         // runs from the queue: workgroups that share a CU drift apart by a
         // tenth of the kernel's time, and equal runs leave the CUs part empty
@@ -849,7 +854,7 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
         // 147; 1024, 113 segments 610, 587, 595; 4096, 525 segments 2580, 2425,
         // 2392).  A knob off its default is taken as it is.
         uint64_t per = (uint64_t)par.items_per_wg;
-        if (col && par.items_per_wg == Params().items_per_wg)
+        if (col && par.adapt && par.items_per_wg == Params().items_per_wg)
             per = std::min<uint64_t>(12, std::max<uint64_t>(per, per_wg / 16));
         const uint64_t target = std::max<uint64_t>(1, resident * per);
         const uint64_t run = std::min<uint64_t>(
@@ -1703,6 +1708,10 @@ int esq_set_param(const char* name, int64_t value)
         if (value < 0 || value > 1)
             return fail(ESQ_EINVAL, "priority must be 0 or 1");
         g_par.priority = value;
+    } else if (n == "adapt") {
+        if (value < 0 || value > 1)
+            return fail(ESQ_EINVAL, "adapt must be 0 or 1");
+        g_par.adapt = value;
     } else {
         return fail(ESQ_EINVAL, "unknown parameter " + n);
     }
@@ -1710,7 +1719,7 @@ int esq_set_param(const char* name, int64_t value)
     // (tail_cap: see seg_log2_for)
     if (g_ctx && (n == "seg_log2" || n == "kh" || n == "medium_max" || n == "entry_hits" ||
                   n == "block" || n == "per_n_block" || n == "sieve_seg_log2" || n == "sieve_block" ||
-                  n == "tail_cap")) {
+                  n == "tail_cap" || n == "adapt")) {
         hipError_t e = hipSetDevice(g_ctx->device);
         if (e != hipSuccess)
             return hip_fail(e, "hipSetDevice");
@@ -1742,6 +1751,7 @@ int64_t esq_get_param(const char* name)
     if (n == "stagger") return g_par.stagger;
     if (n == "priority") return g_par.priority;
     if (n == "cof_weight") return g_par.cof_weight;
+    if (n == "adapt") return g_par.adapt;
     return -1;
 }
 

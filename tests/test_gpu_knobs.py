@@ -113,3 +113,45 @@ def test_marks_per_task_are_as_many_as_set():
     print("marking: %.2f of the kernel, %.2f with 4096 marks a task" % (share, slow))
     assert s == r
     assert share < 0.5 < slow
+
+
+@pytest.fixture
+def as_set():
+    esq.set_param("adapt", 0)
+    yield
+    esq.set_param("adapt", 1)
+
+
+def segments_of_a_call(lo, n):
+    """Segments of the form that has more, from the figure's growth by 500 slots
+    each."""
+    f = {}
+    for slots in (500, 1000):
+        esq.set_param("bucket_cap", slots)
+        f[slots] = esq.scratch_bytes([lo], [lo + 2 * n])
+    esq.set_param("bucket_cap", 0)
+    return (f[1000] - f[500]) / 2000
+
+
+def test_default_values_are_taken_as_set_where_nothing_adapts(as_set):
+    """Segments of 2^18 for a short per-n call (128 of 2^14 otherwise), four runs
+    a workgroup for a batch (twelve otherwise), and the same results."""
+    lo, n = (1 << 49) + 1, 1 << 21
+    assert segments_of_a_call(lo, n) == pytest.approx(9, abs=0.3)
+    ivs = [lo + (i << 28) for i in range(4096)], [lo + (i << 28) + (1 << 27) for i in range(4096)]
+    esq.set_param("bucket_cap", 64)
+    equal = esq.scratch_bytes(*ivs)
+    esq.set_param("adapt", 1)
+    runs = esq.scratch_bytes(*ivs)
+    esq.set_param("bucket_cap", 0)
+    assert runs - equal > 16 * 4000
+    assert segments_of_a_call(lo, n) > 120
+
+    def results():
+        p = esq.verify_range(lo, lo + 2 * n, per_n=True)
+        return (p.pop("per_n"), esq.sieve_segment(lo, lo + (1 << 21))[2], p,
+                esq.verify_range(lo, lo + (1 << 34)), noalloc_call(lo, lo + 2 * n, 3, False, 16))
+    adapted = results()
+    esq.set_param("adapt", 0)
+    for a, b in zip(adapted, results()):
+        assert torch.equal(a, b) if torch.is_tensor(a) else a == b
