@@ -566,10 +566,16 @@ int prebuild_med_tables(Ctx* c, const Params& par)
 }
 
 // Launches with at least so many hits of large primes expected have
-// k_bucket_own find them (see there): below it, k_bucket's counters in memory
-// see few enough hits, and its primes spread over more of the chip (10^8 odd n,
-// 3e3 hits: 6.7 us, 10.6 with k_bucket_own; 2^31, 6e4 hits: 11.8 and 9.5; 1024
-// intervals, 9e5 hits: 110 and 63).
+// k_bucket_own find them (see there).  Below it k_bucket's counters in memory see
+// few enough hits, and its primes spread over more of the chip, while each
+// workgroup of k_bucket_own goes through all of them; that it clears too, so that
+// k_prepare's launch falls away, is counted: whole calls near 2^49, alone on the
+// device, k_bucket / k_bucket_own: 2^26 odd n (1.9e3 hits) 47.6 / 53.1 us, sieved
+// 35.0 / 40.1; 2^29 (1.5e4) 61.2 / 63.4, 50.5 / 52.2; 2^30 (3.1e4) 71.9 / 74.3, 65.7
+// / 65.2; 2^31 (6.2e4) 91.9 / 91.6, 94.0 / 91.8; in a stream of calls they are level
+// from 1.5e4 to 4e4 hits.  Near 2^40, with a twentieth of the primes, k_bucket_own
+// is ahead from 2e3 hits on (2^28 odd n 56.0 / 52.8); 1024 intervals, 9e5 hits:
+// the kernel alone 110 / 57.
 constexpr double kOwnMinHits = 4e4;
 
 // One interval to process, in odd-index terms: verify -> the n-indices
@@ -832,10 +838,15 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
         // tenth of the kernel's time, and equal runs leave the CUs part empty
         // at the end.  Below 24 segments a workgroup a run's own start (first
         // hits, queue) costs what the balance gives (16 segments a workgroup:
-        // 90 us equal, 98 cut).  By segments a workgroup, long runs of three
-        // quarters and short ones of a twelfth / of a half and a sixth / an
-        // eighth: 24 134, 134, 135 us; 33 165, 162.6, 164.5; 49 227, 222, 219;
-        // 132 581, 568, 553.
+        // 90 us equal, 98 cut).  Long runs of three quarters and short ones of a
+        // twelfth: 49 segments a workgroup 227 us, of a half and an eighth 219;
+        // 132 581 and 553.  Short runs of a sixth / an eighth / a twelfth of a
+        // workgroup's share, below 2^50, by segments a workgroup: 24 124.3, 128.1,
+        // 134.3 us; 29 144.1, 146.5, 160.0; 33 160.6, 162.1, 176.8; 37 175.1,
+        // 178.9, 179.2; 39 184.4, 185.9, 188.3; 42 196.2, 193.4, 198.8; 52 237.8,
+        // 232.1, 237.5; 80 350.5, 346.2, 351.2; 130 555.8, 547.5, 557.2 (below 2^42
+        // the same): below 40 an eighth is three or four segments, and the runs'
+        // starts outweigh the balance.
         run_long = (uint32_t)std::min<uint64_t>(kFlushSegs, per_wg / 2);
         run_short = (uint32_t)std::min<uint64_t>(kFlushSegs, per_wg / (per_wg < 40 ? 6 : 8));
         const uint64_t rest = nseg_total - resident * run_long;
