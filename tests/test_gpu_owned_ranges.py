@@ -1,0 +1,93 @@
+"""k_bucket_own's branches that ordinary calls do not take: integer reductions
+(odd indices from 2^52 on), cofactors of n up to 2^56, and lists of primes and
+cofactors longer than their room in LDS.  Whole-number results: equal to calls
+too short for owned segments, or to other segments."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_2411_01964_amd import esq
+from tests.test_gpu_parity import DEFAULTS, assert_same, knobs
+
+pytestmark = pytest.mark.gpu
+
+SEG = (1 << 18) - 4096
+
+
+@pytest.fixture(scope="module", autouse=True)
+def lib_ready():
+    esq.init(0, esq.ESQ_MAX_HI)
+    knobs()
+    yield
+    for k, v in DEFAULTS.items():
+        esq.set_param(k, v)
+
+
+def joined(lo, n, parts, kmax=0):
+    """hist and per-n bytes of the interval in equal parts."""
+    hist, bytes_ = [0] * 65, []
+    for i in range(parts):
+        r = esq.verify_range(lo + 2 * (n * i // parts), lo + 2 * (n * (i + 1) // parts), per_n=True)
+        hist = [a + b for a, b in zip(hist, r["hist"])]
+        bytes_.append(r["per_n"])
+    return hist, torch.cat(bytes_)
+
+
+@pytest.mark.parametrize("at", [1 << 53, 1 << 55, esq.ESQ_MAX_HI])
+def test_integer_reductions_equal_short_calls(at):
+    """With the primes from 17 on all counted as large, 2^22 odd n have about
+    7e4 hits, past the 4e4 of owned segments; a sixteenth of them has too few.
+    The upper half lies past odd index 2^52 for at = 2^53, which decides for
+    the whole call."""
+    knobs(medium_max=11)
+    n = 1 << 22
+    lo = at - n + 1 if at < esq.ESQ_MAX_HI else at - 2 * n - 1
+    hist, per_n = joined(lo, n, 16)
+    s = esq.verify_range(lo, lo + 2 * n)                        # column layout
+    p = esq.verify_range(lo, lo + 2 * n, per_n=True)            # row layout
+    assert s["hist"] == hist and p["hist"] == hist
+    assert s["records"] == p["records"] and s["ksum"] == p["ksum"]
+    assert torch.equal(p["per_n"], per_n)
+    whole = esq.sieve_segment(lo, lo + 2 * n)[2]
+    step = n // 16
+    words = torch.cat([esq.sieve_segment(lo + 2 * i * step, lo + 2 * (i + 1) * step)[2] for i in range(16)])
+    assert torch.equal(whole, words)
+    knobs()
+
+
+@pytest.mark.parametrize("at", [1 << 53, esq.ESQ_MAX_HI])
+@pytest.mark.parametrize("kw", [dict(), dict(medium_max=11)])
+def test_the_column_layout_past_2pow50(at, kw):
+    """Against the row layout on whole segments, and against the oracle on the
+    last few hundred n."""
+    knobs(**kw)
+    n = 5 * SEG + 4097
+    lo = at - 2 * n - 1
+    s = esq.verify_range(lo, lo + 2 * n)
+    p = esq.verify_range(lo, lo + 2 * n, per_n=True)
+    k = p.pop("per_n")
+    assert s == p
+    a = lo + 2 * (n - 300)
+    o = oracle.verify_range(a, lo + 2 * n, per_n=True)
+    assert np.array_equal(k[-300:].cpu().numpy(), o["per_n"])
+    assert_same(esq.verify_range(a, lo + 2 * n, exceptions_cap=16), o, per_n=False)
+    knobs()
+
+
+@pytest.mark.parametrize("weight", [60, 1])
+def test_lists_longer_than_their_room(weight):
+    """2^36 odd n in segments of 2^20: a workgroup owns 256 of them, 2^28
+    numbers, with a hit for each of the 1336 primes from 4093 to 2^14 and for
+    1050 to 1400 above (room for 2048); at cof_weight 1 the cofactors take over
+    from 2^15.5, 5800 of them with an integer in their range.  Against the
+    column layout's segments."""
+    n = 1 << 36
+    lo = (1 << 50) - 2 * n + 1
+    want = esq.verify_range(lo, 1 << 50)
+    knobs(seg_log2=20)
+    esq.set_param("cof_weight", weight)
+    got = esq.verify_range(lo, 1 << 50)
+    esq.set_param("cof_weight", 60)
+    knobs()
+    assert got == want
