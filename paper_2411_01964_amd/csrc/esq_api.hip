@@ -670,8 +670,8 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
         nseg_total += nseg;
         if (nseg_total > 0x7fffffffull)
             return fail(ESQ_ERANGE, "too many segments in one call");
-        v.wheel_base0 = col ? floor_mod(v.A0 - (int64_t)hlo * 64 - 1, kWheelPeriod)
-                            : wheel_base(v.A0 - (int64_t)hlo * 64);
+        if (!col)
+            v.wheel_base0 = wheel_base(v.A0 - (int64_t)hlo * 64);
         pmax_all = std::max(pmax_all, pmax[i]);
     }
 

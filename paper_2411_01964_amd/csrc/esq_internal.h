@@ -74,11 +74,11 @@ struct Acc {
 
 // One interval of a launch.
 struct Interval {
-    int64_t A0;             // odd index of segment 0's first main bit (multiple of 64)
+    int64_t A0;             // odd index of segment 0's first main bit (row layout: multiple of 64; column layout: I0)
     uint64_t I0, I1;        // verify: odd indices of the n examined; sieve: of the output bits
     uint32_t nseg;          // segments
     uint32_t seg_base;      // global index of segment 0 (bucket slots)
-    uint32_t wheel_base0;   // floor((A0 - 64 hlo_words) / 64) mod kWheelPeriod
+    uint32_t wheel_base0;   // row layout: floor((A0 - 64 hlo_words) / 64) mod kWheelPeriod
     uint32_t pmax_end;      // primes[0 .. pmax_end) are all the primes this interval needs
     uint32_t b_direct_end;  // bucket primes by first hit: primes[med_end .. b_direct_end)
     uint32_t n_cof;         // odd cofactors j = 1, 3, ... for primes from b_direct_end on
