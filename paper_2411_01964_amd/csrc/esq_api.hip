@@ -2,10 +2,11 @@
 //
 // The library keeps, per process, one context on one device: the odd primes
 // up to isqrt(max_hi) (Algorithm 1's prime list, Section 3 of the paper), the
-// pattern table of odd multiples of 9, 25, 49 and 121, and cached tables for
-// the medium primes.  Each call plans its intervals and segments on the host,
-// allocates scratch in stream order on the caller's stream, enqueues the
-// kernels and returns; nothing here waits for the device.
+// pattern tables of odd multiples of 9, 25, 49 and of 121, 169, and tables for the
+// medium primes.  Each call plans its intervals and segments on the host, takes
+// scratch (a kept block, or memory in the stream's order), enqueues the kernels
+// and returns; nothing here waits for the device (the tables are made at set-up,
+// by esq_init and esq_set_param).
 #include <algorithm>
 #include <cmath>
 #include <cstring>

@@ -94,7 +94,7 @@ struct Interval {
 // it marks f + v q + t c q, t >= 0, of medium prime idx (0 = the prime 17),
 // f its first hit in the region.  In the column layout y is the step scaled
 // by 2^(32 - kColLog2), or 2^32 - 1 where the step is no shorter than the region,
-// and only primes with more than one task have any.
+// and only primes with more than kColSingle marks have any.
 
 // Geometry and resources shared by every interval of a launch.
 struct Launch {

@@ -230,9 +230,9 @@ __device__ __forceinline__ uint64_t isqrt_floor(uint64_t x)
     return r;
 }
 
-// first_hit in doubles, for |B0| < 2^52 and q < 2^41, inv close to 1 / q: the
-// quotient's floor is off by at most one, the remainder's fma is exact, and
-// two corrections finish it.  A tenth of the issue time of the 64-bit integer
+// first_hit in doubles, for |B0| < 2^52, 17^2 <= q < 2^41 and inv = recip_d(q): the
+// quotient is below 2^44, so its error below 2^44 2^-46 = 1/4 and its floor off
+// by at most one; the remainder's fma is exact, and two corrections finish it.  A tenth of the issue time of the 64-bit integer
 // reduction, whose multiplies run at a quarter of the rate or less.
 __device__ __forceinline__ double first_hit_d(double B0, double q, double inv)
 {
@@ -242,7 +242,8 @@ __device__ __forceinline__ double first_hit_d(double B0, double q, double inv)
     return r >= q ? r - q : r;
 }
 
-// 1 / q to within a few units in the last place
+// 1 / q to within a relative 2^-46: the hardware's estimate is good to 2^-23 (2^29
+// units in the last place), and a Newton step squares that.
 __device__ __forceinline__ double recip_d(double q)
 {
     const double y = __builtin_amdgcn_rcp(q);
@@ -316,8 +317,10 @@ __device__ __forceinline__ void bucket_emit(const Launch& L, uint32_t seg_base, 
 
 // The odd cofactor j's odd multiples j p^2 in the regions whose least and
 // largest odd number have the square roots sqrt_lo and sqrt_hi: the p form one
-// range, empty for most j when the regions are short.  Its ends, to within
-// 1e-6 (p < 2^28), and whether an integer no smaller than p_cof lies in it.
+// range, empty for most j when the regions are short.  Its ends, and whether an
+// integer no smaller than p_cof lies in it.  The estimate of 1 / sqrt(j) is good
+// to 2^-23, after a Newton step to 1.5 2^-46, so the ends (below 2^28) to 6e-6: the
+// 1e-4 that they are moved outwards by covers it.
 __device__ __forceinline__ bool cofactor_range(uint64_t j, double sqrt_lo, double sqrt_hi, uint32_t p_cof,
                                                double* lo_d, double* hi_d)
 {
@@ -1529,8 +1532,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(MODE == 0 
 // Per 64-n word the row layout's summary form issues 52 vector instructions
 // (30 in the search, a third of them half-rate funnel shifts) and 31 scalar
 // ones; here it is 39 and 18, of which the search has 23 (8 popcounts, 8
-// ANDs).  The vector units are busy for about 0.6 of the time, the LDS for
-// 0.47; the rest are barriers and latencies of eight waves a SIMD, which is
+// ANDs).  The vector units are busy for about 0.7 of the time, the LDS for
+// 0.5; the rest are barriers and latencies of eight waves a SIMD, which is
 // why block size, region length and trip counts are constants and the rare
 // paths (first segments, deep n) have loops of their own: with runtime trip
 // counts and the offers in the common path the same method took 204 us.
@@ -1777,7 +1780,7 @@ __global__ __launch_bounds__(kColBlock) __attribute__((amdgpu_waves_per_eu(8))) 
                     run_task(task, task_min);
                 for (uint32_t e = tid + T; e < n_tasks; e += T)
                     run_task(lp->tasks[e], rfl(lp->task_min[e >> 6]));
-                // the other medium primes, at most entry_hits marks each, by
+                // the other medium primes, at most kColSingle marks each, by
                 // the lanes in reverse, away from the longest tasks
                 for (uint32_t i = n_multi + (T - 1 - tid); i < nmed; i += T) {
                     const uint2 qs = s_medq[i];

@@ -129,7 +129,9 @@ def scan(lo, hi, chunk=1 << 40, checkpoint=None, kmax=0, exceptions_cap=1024,
     verify_async(lo, hi) must enqueue one chunk and return an object whose
     result() gives the chunk's summary dict; the default runs
     esq_verify_range on the GPU.  The next chunk is enqueued before the
-    previous one's result is read, so the device never waits for the host.
+    previous one's result is read; on one stream that read waits for the next
+    chunk too, so the device stands idle once every two chunks, while the host
+    merges and enqueues.
     Returns the merged summary."""
     if verify_async is None:
         verify_async = _gpu_verify_async(kmax, exceptions_cap)
