@@ -241,7 +241,10 @@ def sieve_phase(n, kernel_s, ph, ceil, traffic):
     odd multiple of p^2, p >= 17) against the ds_or_b32 ceiling, search (the
     algorithmic VALU operations, half ANDs, half popcounts) against the measured
     mix of those rates.  The sieve phase (init + marking) carries the paper's
-    LDS traffic against the measured LDS peak."""
+    LDS traffic against the measured LDS peak: over its share of the kernel's
+    time (achieved_GBps, frac_measured, frac_nominal: the target for the sieve
+    phase is stated so, though the CU's other workgroups use the LDS meanwhile),
+    and over the whole kernel like the others (frac_measured_of_kernel)."""
     from paper_2411_01964_amd import esq
 
     tot = max(1, sum(ph.values()))
@@ -269,6 +272,7 @@ def sieve_phase(n, kernel_s, ph, ceil, traffic):
         "peak_measured_GBps": lds_meas / 1e9,
         "frac_measured": SIEVE_LDS_BYTES_PER_N * n / sieve_s / lds_meas,
         "frac_nominal": SIEVE_LDS_BYTES_PER_N * n / sieve_s / LDS_PEAK,
+        "frac_measured_of_kernel": SIEVE_LDS_BYTES_PER_N * n / kernel_s / lds_meas,
         "init": {"ms": t_init * 1e3, "bound": "l2 read", "l2_bytes": l2_bytes,
                  "achieved_GBps": l2_bytes / kernel_s / 1e9,
                  "ceiling_GBps": ceil["l2_read_Bps"] / 1e9,
