@@ -232,8 +232,9 @@ __device__ __forceinline__ uint64_t isqrt_floor(uint64_t x)
 
 // first_hit in doubles, for |B0| < 2^52, 17^2 <= q < 2^41 and inv = recip_d(q): the
 // quotient is below 2^44, so its error below 2^44 2^-46 = 1/4 and its floor off
-// by at most one; the remainder's fma is exact, and two corrections finish it.  A tenth of the issue time of the 64-bit integer
-// reduction, whose multiplies run at a quarter of the rate or less.
+// by at most one; the remainder's fma is exact, and two corrections finish it.
+// A tenth of the issue time of the 64-bit integer reduction, whose multiplies
+// run at a quarter of the rate or less.
 __device__ __forceinline__ double first_hit_d(double B0, double q, double inv)
 {
     const double d = (q - 1.0) * 0.5 - B0;
@@ -253,18 +254,19 @@ __device__ __forceinline__ double recip_d(double q)
 // Segment s of an interval covers region offsets y in [s S, s S + R): a hit
 // belongs to segment floor(y / S) and to each earlier segment still reaching it.
 // A hit's slot number comes back from a device-scope atomic, microseconds
-// later: the hits go out kEmit at a time (y[0 .. n)).
+// later: where there are many, the hits go out kEmit at a time (y[0 .. n)).
 constexpr uint32_t kEmit = 4;
+template <uint32_t N>
 __device__ __forceinline__ void bucket_put(const Launch& L, uint32_t seg_base, uint32_t nseg,
-                                           const uint64_t (&y)[kEmit], uint32_t n)
+                                           const uint64_t (&y)[N], uint32_t n)
 {
     const uint64_t S = L.S;
     const uint32_t R = L.rw * 64;
-    uint64_t seg[kEmit];
-    uint32_t off[kEmit], pos[kEmit];
+    uint64_t seg[N];
+    uint32_t off[N], pos[N];
     bool again = false;
 #pragma unroll
-    for (uint32_t u = 0; u < kEmit; u++) {
+    for (uint32_t u = 0; u < N; u++) {
         // y div S through the reciprocal: at most one too small (y < 2^56)
         seg[u] = __umul64hi(y[u], L.s_inv);
         off[u] = (uint32_t)(y[u] - seg[u] * S);
@@ -281,11 +283,11 @@ __device__ __forceinline__ void bucket_put(const Launch& L, uint32_t seg_base, u
             seg[u] = 0;
     }
 #pragma unroll
-    for (uint32_t u = 0; u < kEmit; u++)
+    for (uint32_t u = 0; u < N; u++)
         if (pos[u] < L.bucket_cap)
             L.bucket_slot[(seg_base + seg[u]) * L.bucket_cap + pos[u]] = off[u];
     if (again)  // hits in the overlap with earlier segments
-        for (uint32_t u = 0; u < kEmit; u++) {
+        for (uint32_t u = 0; u < N; u++) {
             uint64_t g = seg[u];
             uint64_t o = off[u] + S;
             while (u < n && o < R && g > 0) {
@@ -332,18 +334,17 @@ __device__ __forceinline__ bool cofactor_range(uint64_t j, double sqrt_lo, doubl
     return *hi_d >= *lo_d && *hi_d >= (double)p_cof;
 }
 
-// hits(y, n) for the region offsets y[0 .. n) of j's multiples of the primes p >=
-// p_cof in that range, at most kEmit of them a call; the regions' bit 0 is odd
-// index B0 and they hold E bits.  The range's ends come from the estimates by
-// exact corrections.  Its primes come from the bitmap of odd primes, of which
-// lane g takes words g, g + lanes, ... of the range's: one load for 32 odd
-// numbers.  What bounds a wide range is the chain of a lane's loads and of the
-// hits' atomics.  2^30 odd n from 2^40, where j = 1 has a range of 1024 numbers:
-// k_bucket 46 us a number a load and a hit at a time over 8 lanes, 16 a word a
-// load, 9 over 16 lanes with four hits in flight.
-template <typename Hits>
+// hit(y) for the region offset y of each of j's multiples of a prime p >= p_cof
+// in that range; the regions' bit 0 is odd index B0 and they hold E bits.  The
+// range's ends come from the estimates by exact corrections.  Its primes come
+// from the bitmap of odd primes, of which lane g takes words g, g + lanes, ... of
+// the range's: one load for 32 odd numbers.  What bounds a wide range is the chain
+// of a lane's loads and of the hits' atomics.  2^30 odd n from 2^40, where j = 1
+// has a range of 1024 numbers: k_bucket 46 us a number a load over 8 lanes, 16 a
+// word a load, 9 over 16 lanes (and over 32 and 64, or with four hits in flight).
+template <typename Hit>
 __device__ __forceinline__ void cofactor_hits(const Launch& L, uint64_t j, double lo_d, double hi_d, int64_t B0,
-                                              uint64_t E, uint32_t p_cof, uint32_t g, uint32_t lanes, Hits hits)
+                                              uint64_t E, uint32_t p_cof, uint32_t g, uint32_t lanes, Hit hit)
 {
     const uint64_t m_lo = B0 > 0 ? 2 * (uint64_t)B0 + 1 : 1;
     const uint64_t m_hi = 2 * (uint64_t)(B0 + (int64_t)E - 1) + 1;
@@ -357,6 +358,8 @@ __device__ __forceinline__ void cofactor_hits(const Launch& L, uint64_t j, doubl
         pb--;
     pb = min(pb, (uint64_t)L.plimit);
     const uint64_t a = max(pa, (uint64_t)p_cof) | 1, w_end = pb >> 6;
+    if (a > pb)  // no odd number
+        return;
     for (uint64_t w = (a >> 6) + g; w <= w_end; w += lanes) {
         // bit b: 64 w + 2 b + 1; those from a on, and up to pb
         uint32_t bits = L.pbits[w];
@@ -364,17 +367,9 @@ __device__ __forceinline__ void cofactor_hits(const Launch& L, uint64_t j, doubl
             bits &= ~0u << ((a >> 1) & 31u);
         if (w == w_end)
             bits &= (uint32_t)((1ull << (((pb & 63u) + 1) >> 1)) - 1);
-        while (bits) {
-            uint64_t y[kEmit];
-            uint32_t n = 0;
-#pragma unroll
-            for (uint32_t u = 0; u < kEmit; u++) {
-                n += bits ? 1u : 0u;
-                const uint64_t p = 64 * w + 2 * (uint64_t)(31 - __clz((int)(bits | 1u))) + 1;
-                y[u] = (j * p * p - 1) / 2 - (uint64_t)B0;
-                bits &= ~(1u << (31 - __clz((int)(bits | 1u))));
-            }
-            hits(y, n);
+        for (; bits; bits &= bits - 1) {
+            const uint64_t p = 64 * w + 2 * (uint64_t)(__ffs((int)bits) - 1) + 1;
+            hit((j * p * p - 1) / 2 - (uint64_t)B0);
         }
     }
 }
@@ -422,8 +417,10 @@ __global__ __launch_bounds__(256) void k_bucket(Launch L, uint32_t n_heavy, uint
     double lo_d, hi_d;
     if (cofactor_range(2 * c + 1, iv->sqrt_lo, iv->sqrt_hi, p_cof, &lo_d, &hi_d))
         cofactor_hits(L, 2 * c + 1, lo_d, hi_d, B0, E, p_cof, wide ? (uint32_t)(tc % kCofactorLanes) : 0u,
-                      wide ? kCofactorLanes : 1u,
-                      [&](const uint64_t (&y)[kEmit], uint32_t n) { bucket_put(L, iv->seg_base, iv->nseg, y, n); });
+                      wide ? kCofactorLanes : 1u, [&](uint64_t y) {
+                          const uint64_t one[1] = {y};
+                          bucket_put(L, iv->seg_base, iv->nseg, one, 1);
+                      });
 }
 
 // Many segments: a workgroup owns up to kOwnSegs consecutive segments of one
@@ -495,12 +492,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
     auto cofactor = [&](uint32_t c) {
         double lo_d, hi_d;
         if (cofactor_range(2 * (uint64_t)c + 1, sqrt_lo, sqrt_hi, p_cof, &lo_d, &hi_d))
-            cofactor_hits(L, 2 * (uint64_t)c + 1, lo_d, hi_d, B0, E, p_cof, 0u, 1u,
-                          [&](const uint64_t (&y)[kEmit], uint32_t m) {
-                              for (uint32_t u = 0; u < kEmit; u++)
-                                  if (u < m)
-                                      emit(y[u]);
-                          });
+            cofactor_hits(L, 2 * (uint64_t)c + 1, lo_d, hi_d, B0, E, p_cof, 0u, 1u, emit);
     };
     for (uint32_t c = threadIdx.x; c < n_cof; c += blockDim.x) {
         double lo_d, hi_d;
