@@ -2,6 +2,8 @@
 (odd indices from 2^52 on), cofactors of n up to 2^56, and lists of primes and
 cofactors longer than their room in LDS.  Whole-number results: equal to calls
 too short for owned segments, or to other segments."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -91,3 +93,46 @@ def test_lists_longer_than_their_room(weight):
     esq.set_param("cof_weight", 60)
     knobs()
     assert got == want
+
+
+def batch_time(count, n, top):
+    """Seconds per launch of a prepared batch of count intervals of n odd n each
+    below 2^top."""
+    rng = np.random.default_rng(7)
+    lo = [int(rng.integers(1 << (top - 2), (1 << (top - 1)) - n)) * 2 + 1 for _ in range(count)]
+    pb = esq.PreparedBatch(lo, [a + 2 * n for a in lo])
+    best = 1e9
+    for _ in range(5):
+        pb.launch(graph=True)
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        for _ in range(10):
+            pb.launch(graph=True)
+        torch.cuda.synchronize()
+        best = min(best, (time.perf_counter() - t0) / 10)
+    pb.close()
+    return best
+
+
+def test_wide_cofactor_ranges_cost_no_more_than_narrow_ones():
+    """512 intervals of 2^24 odd n: near 2^28 the few cofactors have ranges of a
+    thousand numbers in a workgroup's segments, near 2^40 of eight; the segment
+    kernel's work is the same.  A lane for each range made the batch a third
+    slower."""
+    wide, narrow = batch_time(512, 1 << 24, 28), batch_time(512, 1 << 24, 40)
+    print("us per batch: %.1f with wide ranges, %.1f with narrow ones" % (wide * 1e6, narrow * 1e6))
+    assert wide < 1.15 * narrow
+
+
+def test_wide_cofactor_ranges_equal_the_row_layout():
+    """8 intervals of 2^28 odd n and 2^31 in one, near 2^33."""
+    lo = [(1 << 32) + (i << 29) + 12345 for i in range(8)]
+    got = esq.verify_batch(lo, [a + (1 << 29) for a in lo])
+    one = esq.verify_range(lo[0], lo[0] + (1 << 32))
+    knobs(seg_log2=16)
+    want = esq.verify_batch(lo, [a + (1 << 29) for a in lo])
+    knobs(seg_log2=17)
+    whole = esq.verify_range(lo[0], lo[0] + (1 << 32))
+    knobs()
+    assert got == want
+    assert one == whole
