@@ -578,6 +578,14 @@ int prebuild_med_tables(Ctx* c, const Params& par)
 // is ahead from 2e3 hits on (2^28 odd n 56.0 / 52.8); 1024 intervals, 9e5 hits:
 // the kernel alone 110 / 57.
 constexpr double kOwnMinHits = 4e4;
+// Of more intervals than two a CU, each a workgroup of k_bucket_own at least, the
+// workgroups' starts (8 ns each, as many run at once) outweigh what they save
+// where there are few primes to go through: 8000 intervals of 2^12 odd n,
+// k_bucket / k_bucket_own, the whole batch: near 2^30 (3e3 primes) 163 / 207 us, 2^34
+// (1.2e4) 184 / 207, 2^36 (2.2e4) 205 / 215, 2^38 (4.2e4) 252 / 223, 2^44 308 / 251;
+// 2000 of 2^20: 2^30 117 / 128, 2^36 125 / 124, 2^38 140 / 125; 512 of 2^22: 2^30 95 / 94.
+constexpr uint32_t kOwnMinPrimes = 30000;
+constexpr uint32_t kMaxGridY = 65535;  // k_bucket has a row of its grid per interval
 
 // One interval to process, in odd-index terms: verify -> the n-indices
 // [I0, I1); sieve -> the m-indices of the output bits.
@@ -702,8 +710,9 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     const uint64_t direct_threads_full =
         (uint64_t)n_live * (uint64_t)(std::max(med_end, prime_upper(c, kCofactorPrime)) - med_end);
     const uint32_t all_end = std::max(med_end, prime_upper(c, pmax_all));
-    const bool own = all_end > med_end && (double)nseg_total * (double)R *
-                                              (c->inv_pref[all_end] - c->inv_pref[med_end]) >= kOwnMinHits;
+    const double hits = (double)nseg_total * (double)R * (c->inv_pref[all_end] - c->inv_pref[med_end]);
+    const bool few_primes = n_live > 2u * (uint32_t)c->n_cu && all_end - med_end < kOwnMinPrimes;
+    const bool own = all_end > med_end && hits >= kOwnMinHits && (!few_primes || n_iv > kMaxGridY);
     if (!sizes_only && (own || direct_threads_full > (uint64_t)c->n_cu * 2048)) {
         double best = 0;
         for (int h = 20; h <= 40; h++) {

@@ -136,3 +136,35 @@ def test_wide_cofactor_ranges_equal_the_row_layout():
     knobs()
     assert got == want
     assert one == whole
+
+
+def test_many_short_intervals_at_low_positions():
+    """8000 intervals of 2^12 odd n: near 2^30 3000 primes are large, near 2^24
+    none (sqrt below 4096), and the rest of the batch's work is the same.  A
+    workgroup each to go through so few made the batch 1.4 times as slow."""
+    some, none = batch_time(8000, 1 << 12, 30), batch_time(8000, 1 << 12, 24)
+    print("us per batch: %.1f with 3000 large primes, %.1f with none" % (some * 1e6, none * 1e6))
+    assert some < 1.25 * none
+
+
+@pytest.mark.parametrize("top", [30, 36, 38])
+def test_many_short_intervals_equal_each_alone(top):
+    """600 intervals: counters in memory below 3e4 large primes, owned segments
+    above (at 3 segments each, past 4e4 hits with medium_max 2047)."""
+    knobs(medium_max=2047)
+    rng = np.random.default_rng(top)
+    n = [int(x) for x in rng.integers(1, 5 << 17, 600)]
+    lo = [int(rng.integers(1 << (top - 2), (1 << (top - 1)) - (5 << 17))) * 2 + 1 for _ in n]
+    got = esq.verify_batch(lo, [a + 2 * k for a, k in zip(lo, n)])
+    for g, a, k in list(zip(got, lo, n))[::7]:
+        w = esq.verify_range(a, a + 2 * k)
+        assert all(g[x] == w[x] for x in g)
+    knobs()
+
+
+def test_more_intervals_than_a_grid_has_rows():
+    """70000 intervals at a low position, whichever form they take."""
+    lo = [(1 << 28) + 1 + 200 * i for i in range(70000)]
+    got = esq.verify_batch(lo, [a + 200 for a in lo])
+    one = esq.verify_range(lo[0], lo[-1] + 200)
+    assert [sum(h) for h in zip(*(g["hist"] for g in got))] == one["hist"]
