@@ -544,13 +544,17 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8))) void 
         for (uint64_t f = s_hit[i], q = (uint64_t)s_prime[i] * s_prime[i]; f < E; f += q)
             emit(f);
     // Few cofactors have all the hits at low positions, in ranges (the widest:
-    // that of j = 1) of more than a word of the bitmap: several lanes each.  2^33
-    // odd n near 2^36: 22.6 us with a lane each, 13.8 so.
-    static_assert((kCofactorLanes & (kCofactorLanes - 1)) == 0, "a power of two");
-    const bool wide = sqrt_hi - sqrt_lo >= 64.0 && c_listed * kCofactorLanes <= blockDim.x;
-    const uint32_t shift = wide ? 31u - __clz((int)kCofactorLanes) : 0u, lanes = 1u << shift;
+    // that of j = 1) of several words of the bitmap: a lane for each word, as far
+    // as there are.  2^33 odd n near 2^36: 22.6 us with a lane for each range,
+    // 13.6 so; from 3 on, where the first workgroup has a range of 8192 numbers,
+    // 360 and 14.8.
+    uint32_t shift = 0;
+    if (sqrt_hi - sqrt_lo >= 64.0)
+        shift = 32u - __clz((int)((sqrt_hi - sqrt_lo) * (1.0 / 64.0)) + 1);
+    while (shift && c_listed << shift > blockDim.x)
+        shift--;
     for (uint32_t i = blockDim.x - 1 - threadIdx.x; i < c_listed << shift; i += blockDim.x)
-        cofactor(s_cof[i >> shift], i & (lanes - 1), lanes);
+        cofactor(s_cof[i >> shift], i & ((1u << shift) - 1), 1u << shift);
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < n; i += blockDim.x)
         L.bucket_cnt[gs + i] = s_cnt[i];

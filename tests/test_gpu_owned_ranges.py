@@ -124,6 +124,25 @@ def test_wide_cofactor_ranges_cost_no_more_than_narrow_ones():
     assert wide < 1.15 * narrow
 
 
+def test_an_interval_from_3_on_costs_no_more_than_a_high_one():
+    """2^33 odd n: from 3 on the first workgroup's cofactor 1 has a range of 8192
+    numbers, which one lane made three times the whole call."""
+    def per_call(lo):
+        best = 1e9
+        for _ in range(5):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(10):
+                esq.verify_range_async(lo, lo + (1 << 34))
+            torch.cuda.synchronize()
+            best = min(best, (time.perf_counter() - t0) / 10)
+        return best
+
+    low, high = per_call(3), per_call((1 << 40) + 1)
+    print("us per call: %.1f from 3, %.1f from 2^40" % (low * 1e6, high * 1e6))
+    assert low < 1.15 * high
+
+
 def test_wide_cofactor_ranges_equal_the_row_layout():
     """8 intervals of 2^28 odd n and 2^31 in one, near 2^33."""
     lo = [(1 << 32) + (i << 29) + 12345 for i in range(8)]
