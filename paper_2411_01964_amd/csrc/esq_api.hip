@@ -761,7 +761,7 @@ int plan(Ctx* c, const Params& par, int mode, uint32_t kmax, const std::vector<R
     }
     // Workgroups of k_bucket_own: one per CU where the intervals allow, each
     // with an even share of one interval's segments (two per CU: 2^33 odd n
-    // 26 us, one: 19).
+    // 23 us, one: 16).
     P->ranges.clear();
     P->n_ranges = 0;
     if (any_bucket && own) {
