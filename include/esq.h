@@ -194,8 +194,9 @@ int esq_verify_batch(uint32_t count, const uint64_t *lo, const uint64_t *hi, uin
  * per-interval descriptors and accumulators.  The caller's outputs
  * (summaries, records, per-n bytes) are not included.  It is the larger of
  * the figures with and without per-n outputs.  For count = 1 it is also the
- * scratch of esq_verify_range on that interval with exceptions_cap = 0.  For admission control by a server: a request is
- * admitted when its scratch and its outputs fit in device memory.
+ * scratch of esq_verify_range on that interval with exceptions_cap = 0.  For
+ * admission control by a server: a request is admitted when its scratch and its
+ * outputs fit in device memory.
  *   count, lo, hi, kmax  as in esq_verify_batch (host arrays)
  *   out_bytes            host, required
  * Synchronous; enqueues nothing.  Errors as esq_verify_batch.
